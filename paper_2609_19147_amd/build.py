@@ -20,8 +20,9 @@ LIB = os.path.join(PKG, "libqs.so")
 PROBE_SRC = os.path.join(CSRC, "ceiling_probe.hip")
 PROBE = os.path.join(PKG, "ceiling_probe")
 
-SOURCES = ["planner.cpp", "api.cpp", "runtime.cpp", "adjoint.cpp", "batch.cpp",
-           "k_tile.hip", "k_dense.hip", "k_sample.hip", "k_stream.hip", "k_plain.hip", "k_reduce.hip"]
+SOURCES = ["planner.cpp", "api.cpp", "runtime.cpp", "expect.cpp", "adjoint.cpp", "batch.cpp",
+           "k_tile.hip", "k_dense.hip", "k_sample.hip", "k_stream.hip", "k_plain.hip", "k_reduce.hip",
+           "k_expect.hip"]
 
 ARCH = os.environ.get("QS_OFFLOAD_ARCH", "gfx950")
 # Packed FP32 instructions are kept out of every kernel.

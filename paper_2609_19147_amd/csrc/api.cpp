@@ -219,6 +219,19 @@ void qs_state::ensure_norm(uint64_t tiles) {
   norm_cap = tiles;
 }
 
+double* qs_state::ensure_expect(size_t doubles) {
+  if (expect_cap >= doubles) return expect_buf;
+  if (expect_buf) {
+    check_hip(hipStreamSynchronize(stream), "hipStreamSynchronize");
+    check_hip(hipFree(expect_buf), "hipFree");
+    expect_buf = nullptr;
+    expect_cap = 0;
+  }
+  check_hip(hipMalloc(&expect_buf, sizeof(double) * doubles), "hipMalloc");
+  expect_cap = doubles;
+  return expect_buf;
+}
+
 void* qs_state::ensure_work_buf(size_t bytes) {
   if (work_cap >= bytes) return work_buf;
   if (work_buf) {
@@ -269,6 +282,7 @@ qs_state::~qs_state() {
   if (red_partials) hipFree(red_partials);
   if (red_out) hipFree(red_out);
   if (norm_part) hipFree(norm_part);
+  if (expect_buf) hipFree(expect_buf);
   free_graphs(*this);
   if (matbuf) hipFree(matbuf);
   if (work_buf) free_amplitudes(work_buf, work_cap);

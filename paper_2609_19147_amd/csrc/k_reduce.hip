@@ -4,6 +4,7 @@
 // sums pairwise, and a second kernel (one workgroup per output) folds the
 // workgroup partials in a fixed order, so results are bitwise repeatable for
 // a given size.
+#include "acc.h"
 #include "kernels.h"
 #include "rho.h"
 
@@ -12,24 +13,6 @@ namespace qs {
 namespace {
 
 constexpr int kThreads = 256;
-
-struct Acc {
-  double s, c;
-};
-
-__device__ __forceinline__ void nadd(Acc& a, double x) {
-  const double t = a.s + x;
-  if (fabs(a.s) >= fabs(x))
-    a.c += (a.s - t) + x;
-  else
-    a.c += (x - t) + a.s;
-  a.s = t;
-}
-__device__ __forceinline__ Acc ncombine(Acc a, const Acc& b) {
-  nadd(a, b.s);
-  a.c += b.c;
-  return a;
-}
 
 template <int NV, class F>
 __global__ void __launch_bounds__(kThreads) reduce_kernel(F f, uint64_t count, double* __restrict__ partials) {

@@ -159,6 +159,50 @@ template <class R>
 void launch_expect_x(const cplx<R>* psi, int n, uint32_t x, const uint32_t* z, const int* ny, int nt,
                      double* partials, double* out, hipStream_t s);
 
+// Pauli terms in sets that share one read of the state (k_expect.hip).  The
+// tile of a set is the state bits [0, L) U hi_bit[]; a window is four tile bits
+// (ascending tile positions, 8 bits each) with groups of terms of one X mask
+// inside it (x over the window's bits), a window's first term at a multiple of
+// four (the terms left free are not read).  Term t: z its Z mask (state bits), zw
+// the part inside the window, over the four window bits (x = 0) or over the
+// three left when the highest bit of x is taken out.  Its value is the sum over
+// one index i of each pair {i, i ^ x} (that bit clear; all i for x = 0) of
+// (-1)^popcount(i & z) times the real (imag: imaginary) part of
+// conj(psi_i) psi_{i ^ x}.  Workgroup b of wsplit n takes the windows
+// w = b mod wsplit of its tiles.  The whole set travels in the kernel arguments.
+constexpr uint32_t kExpectMaxTerms = 256, kExpectMaxGroups = 64;
+struct ExpectWindow {
+  uint32_t bits, g0, g1;
+};
+struct ExpectGroup {
+  uint32_t x, imag, t0, t1;
+};
+struct ExpectTerm {
+  uint32_t z, zw;
+};
+template <class R>
+struct ExpectArgs {
+  const cplx<R>* psi;
+  double* partials;  // (sum, compensation) per workgroup and term
+  uint32_t m, L, n_free, n_tiles, n_win, n_terms, wsplit;
+  uint32_t load_off[8];  // state offset of tile position k 2^(m - 3)
+  uint8_t hi_bit[16], free_bit[32];
+  ExpectWindow win[kExpectMaxGroups];
+  ExpectGroup grp[kExpectMaxGroups];
+  ExpectTerm term[kExpectMaxTerms + 1];  // the kernel reads one ahead
+};
+constexpr uint32_t expect_tile_bits(bool complex128) { return complex128 ? 11 : 12; }
+template <class R> void launch_expect_tiles(const ExpectArgs<R>& A, uint32_t blocks, hipStream_t s);
+// out[k] = the folded sums of the sets' terms, in order.
+constexpr uint32_t kExpectMaxSets = 32;
+struct ExpectFold {
+  const double* partials;
+  uint32_t n_sets;
+  uint32_t n_terms[kExpectMaxSets], n_blocks[kExpectMaxSets];
+  uint64_t off[kExpectMaxSets];  // doubles from partials
+};
+void launch_expect_fold(const ExpectFold& F, double* out, hipStream_t s);
+
 // ---- read-out ----
 // Shot sampling: out[k] = the first index whose cumulative probability exceeds
 // u[k] ||psi||^2 (cumulative sums hierarchical, FP64, fixed order); u and out

@@ -5,7 +5,6 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
-#include <map>
 #include <mutex>
 
 namespace qs {
@@ -867,58 +866,6 @@ double state_infidelity(qs_state& a, qs_state& b) {
   else if (b.dtype == QS_C64) D = distance_t<double, float>(a, b, ar, ai, bs);
   else D = distance_t<double, double>(a, b, ar, ai, bs);
   return std::max(0.0, D * (1.0 - D / 4.0));
-}
-
-std::vector<double> state_expect(qs_state& s, const qs_pauli* terms, size_t n_terms) {
-  const int n = s.n;
-  std::vector<double> out(n_terms, 0.0);
-  std::map<uint32_t, std::vector<size_t>> by_x;
-  std::vector<uint32_t> zb(n_terms);
-  std::vector<int> ny(n_terms);
-  for (size_t t = 0; t < n_terms; ++t) {
-    const qs_pauli& P = terms[t];
-    if (!std::isfinite(P.coeff)) fail(QS_EINVAL, "non-finite Pauli coefficient");
-    if (n < 64 && ((P.x_mask >> n) || (P.z_mask >> n))) fail(QS_EINVAL, "Pauli mask out of range");
-    uint32_t x = 0, z = 0;
-    for (int q = 0; q < n; ++q) {
-      if ((P.x_mask >> q) & 1) x |= 1u << (n - 1 - q);
-      if ((P.z_mask >> q) & 1) z |= 1u << (n - 1 - q);
-    }
-    zb[t] = z;
-    ny[t] = __builtin_popcount(x & z) & 3;
-    by_x[x].push_back(t);
-  }
-  s.ensure_red();
-  for (auto& kv : by_x) {
-    const auto& idx = kv.second;
-    for (size_t c0 = 0; c0 < idx.size(); c0 += kMaxTermsPerLaunch) {
-      int nt = (int)std::min<size_t>(kMaxTermsPerLaunch, idx.size() - c0);
-      uint32_t zz[kMaxTermsPerLaunch];
-      int yy[kMaxTermsPerLaunch];
-      for (int k = 0; k < nt; ++k) {
-        zz[k] = zb[idx[c0 + k]];
-        yy[k] = ny[idx[c0 + k]];
-      }
-      if (kv.first == 0) {
-        if (s.dtype == QS_C64)
-          launch_expect_z<float>((const cplx<float>*)s.cur_ptr(), n, zz, nt, s.red_partials, s.red_out, s.stream);
-        else
-          launch_expect_z<double>((const cplx<double>*)s.cur_ptr(), n, zz, nt, s.red_partials, s.red_out, s.stream);
-      } else {
-        if (s.dtype == QS_C64)
-          launch_expect_x<float>((const cplx<float>*)s.cur_ptr(), n, kv.first, zz, yy, nt, s.red_partials, s.red_out,
-                                 s.stream);
-        else
-          launch_expect_x<double>((const cplx<double>*)s.cur_ptr(), n, kv.first, zz, yy, nt, s.red_partials,
-                                  s.red_out, s.stream);
-      }
-      double o[kMaxTermsPerLaunch];
-      check_hip(hipMemcpyAsync(o, s.red_out, sizeof o, hipMemcpyDeviceToHost, s.stream), "hipMemcpyAsync");
-      s.sync();
-      for (int k = 0; k < nt; ++k) out[idx[c0 + k]] = terms[idx[c0 + k]].coeff * o[k];
-    }
-  }
-  return out;
 }
 
 }  // namespace qs
