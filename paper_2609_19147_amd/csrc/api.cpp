@@ -219,17 +219,17 @@ void qs_state::ensure_norm(uint64_t tiles) {
   norm_cap = tiles;
 }
 
-double* qs_state::ensure_expect(size_t doubles) {
-  if (expect_cap >= doubles) return expect_buf;
-  if (expect_buf) {
+void* qs_state::ensure_scratch(size_t bytes) {
+  if (scratch_cap >= bytes) return scratch_buf;
+  if (scratch_buf) {
     check_hip(hipStreamSynchronize(stream), "hipStreamSynchronize");
-    check_hip(hipFree(expect_buf), "hipFree");
-    expect_buf = nullptr;
-    expect_cap = 0;
+    check_hip(hipFree(scratch_buf), "hipFree");
+    scratch_buf = nullptr;
+    scratch_cap = 0;
   }
-  check_hip(hipMalloc(&expect_buf, sizeof(double) * doubles), "hipMalloc");
-  expect_cap = doubles;
-  return expect_buf;
+  check_hip(hipMalloc(&scratch_buf, bytes), "hipMalloc");
+  scratch_cap = bytes;
+  return scratch_buf;
 }
 
 void* qs_state::ensure_work_buf(size_t bytes) {
@@ -282,7 +282,7 @@ qs_state::~qs_state() {
   if (red_partials) hipFree(red_partials);
   if (red_out) hipFree(red_out);
   if (norm_part) hipFree(norm_part);
-  if (expect_buf) hipFree(expect_buf);
+  if (scratch_buf) hipFree(scratch_buf);
   free_graphs(*this);
   if (matbuf) hipFree(matbuf);
   if (work_buf) free_amplitudes(work_buf, work_cap);
@@ -608,6 +608,42 @@ extern "C" qs_status qs_amplitudes(qs_state* s, const uint64_t* idx, size_t coun
 }
 
 // ---------------------------------------------------------------- read-out
+namespace {
+
+// Device scratch for the length of one call that waits for its stream: the
+// state's own area, or, past kKeptScratch bytes, an allocation of the call.
+struct Scratch {
+  static constexpr size_t kKeptScratch = (size_t)64 << 20;
+  void* p = nullptr;
+  bool own = false;
+  Scratch(qs_state& s, size_t bytes) {
+    if (bytes <= kKeptScratch) {
+      p = s.ensure_scratch(bytes);
+      return;
+    }
+    check_hip(hipMalloc(&p, bytes), "hipMalloc");
+    own = true;
+  }
+  ~Scratch() {
+    if (own) hipFree(p);
+  }
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+};
+
+// The drawn indices to the host, once the total mass they were drawn against
+// is known to be positive and finite (the draws of any other are not returned).
+void copy_draws(qs_state& s, const double* total_dev, const uint64_t* draws_dev, size_t count, uint64_t* out) {
+  double total = 0.0;
+  check_hip(hipMemcpyAsync(&total, total_dev, sizeof total, hipMemcpyDeviceToHost, s.stream), "hipMemcpyAsync");
+  s.sync();
+  if (!(total > 0.0) || !std::isfinite(total)) fail(QS_EINVAL, "the state has no probability mass");
+  check_hip(hipMemcpyAsync(out, draws_dev, count * 8, hipMemcpyDeviceToHost, s.stream), "hipMemcpyAsync");
+  s.sync();
+}
+
+}  // namespace
+
 extern "C" qs_status qs_sample(qs_state* s, const double* u, size_t count, uint64_t* out) {
   return guarded([&] {
     check_state(s);
@@ -615,16 +651,9 @@ extern "C" qs_status qs_sample(qs_state* s, const double* u, size_t count, uint6
     if (!u || !out) fail(QS_EINVAL, "NULL argument");
     for (size_t k = 0; k < count; ++k)
       if (!(u[k] >= 0.0 && u[k] < 1.0)) fail(QS_EINVAL, "uniform numbers must lie in [0, 1)");
-    const double nrm = state_norm2(*s);
-    if (!(nrm > 0.0) || !std::isfinite(nrm)) fail(QS_EINVAL, "the state has no probability mass");
     const size_t nscr = sample_scratch_doubles(s->n);
-    void* buf = nullptr;
-    check_hip(hipMalloc(&buf, (nscr + 2 * count) * 8), "hipMalloc");
-    struct Guard {
-      void* p;
-      ~Guard() { hipFree(p); }
-    } guard{buf};
-    double* scratch = (double*)buf;
+    Scratch buf(*s, (nscr + 2 * count) * 8);
+    double* scratch = (double*)buf.p;
     double* du = scratch + nscr;
     uint64_t* dout = (uint64_t*)(du + count);
     check_hip(hipMemcpyAsync(du, u, count * 8, hipMemcpyHostToDevice, s->stream), "hipMemcpyAsync");
@@ -632,8 +661,7 @@ extern "C" qs_status qs_sample(qs_state* s, const double* u, size_t count, uint6
       launch_sample<float>((const cplx<float>*)s->cur_ptr(), s->n, du, count, dout, scratch, s->stream);
     else
       launch_sample<double>((const cplx<double>*)s->cur_ptr(), s->n, du, count, dout, scratch, s->stream);
-    check_hip(hipMemcpyAsync(out, dout, count * 8, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
-    s->sync();
+    copy_draws(*s, scratch + nscr - 1, dout, count, out);
   });
 }
 
@@ -653,22 +681,12 @@ extern "C" qs_status qs_sample_noalloc(qs_state* s, const double* u, size_t coun
     for (size_t k = 0; k < count; ++k)
       if (!(u[k] >= 0.0 && u[k] < 1.0)) fail(QS_EINVAL, "uniform numbers must lie in [0, 1)");
     const NoAllocSampleScratch S = noalloc_sample_scratch(s->device);
-    const uint64_t N = 1ull << s->n;
-    if (s->dtype == QS_C64)
-      launch_norm2<float>((const cplx<float>*)s->cur_ptr(), N, S.norm_partials, S.norm_out, s->stream);
-    else
-      launch_norm2<double>((const cplx<double>*)s->cur_ptr(), N, S.norm_partials, S.norm_out, s->stream);
-    double nrm = 0.0;
-    check_hip(hipMemcpyAsync(&nrm, S.norm_out, sizeof nrm, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
-    s->sync();
-    if (!(nrm > 0.0) || !std::isfinite(nrm)) fail(QS_EINVAL, "the state has no probability mass");
     check_hip(hipMemcpyAsync(S.u, u, count * 8, hipMemcpyHostToDevice, s->stream), "hipMemcpyAsync");
     if (s->dtype == QS_C64)
       launch_sample<float>((const cplx<float>*)s->cur_ptr(), s->n, S.u, count, S.out, S.sums, s->stream);
     else
       launch_sample<double>((const cplx<double>*)s->cur_ptr(), s->n, S.u, count, S.out, S.sums, s->stream);
-    check_hip(hipMemcpyAsync(out, S.out, count * 8, hipMemcpyDeviceToHost, s->stream), "hipMemcpyAsync");
-    s->sync();
+    copy_draws(*s, S.sums + sample_scratch_doubles(s->n) - 1, S.out, count, out);
   });
 }
 
@@ -688,13 +706,8 @@ extern "C" qs_status qs_marginal(qs_state* s, uint64_t qubit_mask, double* out) 
       if ((qubit_mask >> (s->n - 1 - b)) & 1) sel[m++] = b;
     const MarginalArgs A = marginal_geometry(s->n, sel, k);
     const size_t np = marginal_partials(A), bins = (size_t)1 << k;
-    void* buf = nullptr;
-    check_hip(hipMalloc(&buf, (np + bins) * 8), "hipMalloc");
-    struct Guard {
-      void* p;
-      ~Guard() { hipFree(p); }
-    } guard{buf};
-    double* part = (double*)buf;
+    Scratch buf(*s, (np + bins) * 8);
+    double* part = (double*)buf.p;
     double* dout = part + np;
     if (s->dtype == QS_C64)
       launch_marginal<float>((const cplx<float>*)s->cur_ptr(), A, part, dout, s->stream);

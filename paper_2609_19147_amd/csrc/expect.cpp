@@ -165,7 +165,7 @@ void expect_tiled(qs_state& s, const std::vector<Term>& terms, std::vector<doubl
       F.off[k] = doubles;
       doubles += 2ull * F.n_blocks[k] * A.n_terms;
     }
-    double* buf = s.ensure_expect(order.size() + doubles);
+    double* buf = (double*)s.ensure_scratch((order.size() + doubles) * sizeof(double));
     F.partials = buf + order.size();
     for (size_t k = 0; k < ns; ++k) {
       args[k].psi = (const cplx<R>*)s.cur_ptr();

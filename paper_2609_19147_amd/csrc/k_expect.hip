@@ -26,6 +26,7 @@
 // (three sets) 0.96 ms at 26 qubits, slower from 25 down.
 #include "acc.h"
 #include "kernels.h"
+#include "lanes.h"
 
 namespace qs {
 
@@ -52,37 +53,12 @@ __device__ __forceinline__ double contract(const double (&q)[1 << kBits], uint32
   return u[0];
 }
 
-// Both words of a double exchanged between registers a and b across halves (or
-// odd and even rows of 16 lanes), then added: lanes 0-31 (even rows) hold a's
-// partial sums, the others b's.
-__device__ __forceinline__ double fold_halves(double a, double b) {
-  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-__device__ __forceinline__ double fold_rows(double a, double b) {
-  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
-  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
-}
-template <int kN>
-__device__ __forceinline__ double add_row_ror(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + kN, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + kN, 0xf, 0xf, false);
-  return v + __hiloint2double(hi, lo);
-}
-
 // Sums four values over the wavefront's lanes at once (register exchanges, no
 // LDS); value r of the first cnt goes to red[(t0 + r) waves + wave].
 __device__ __forceinline__ void flush4(const double (&v)[4], uint32_t cnt, uint32_t lane, double* red, uint32_t t0,
                                        uint32_t waves, uint32_t wave) {
-  // rows 0..3 of 16 lanes: values 0, 2, 1, 3
-  double t = fold_rows(fold_halves(v[0], v[1]), fold_halves(v[2], v[3]));
-  t = add_row_ror<8>(t);
-  t = add_row_ror<4>(t);
-  t = add_row_ror<2>(t);
-  t = add_row_ror<1>(t);
-  const uint32_t row = lane >> 4, r = ((row & 1u) << 1) | (row >> 1);
+  const double t = wave_sum4(v);
+  const uint32_t r = wave_sum4_value(lane);
   if ((lane & 15u) == 0 && r < cnt) red[(t0 + r) * waves + wave] = t;
 }
 
@@ -121,7 +97,7 @@ expect_tiles_kernel(ExpectArgs<R> A) {
       cplx2<R> v[8];
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k)
-        v[k] = *reinterpret_cast<const cplx2<R>*>(A.psi + (base | A.load_off[k]) + my_off);
+        v[k] = ld_nt(reinterpret_cast<const cplx2<R>*>(A.psi + (base | A.load_off[k]) + my_off));
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k)
         *reinterpret_cast<cplx2<R>*>(T + my_lds + lds_off(2u * blockDim.x * k)) = v[k];

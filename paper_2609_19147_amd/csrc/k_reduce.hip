@@ -8,20 +8,41 @@
 #include "kernels.h"
 #include "rho.h"
 
+#include <type_traits>
+
 namespace qs {
 
 namespace {
 
 constexpr int kThreads = 256;
 
+// Functors with a load() of their own have kAhead loads in flight per thread
+// (added in the same order as one at a time).
+template <class F, class = void>
+struct HasLoad : std::false_type {};
+template <class F>
+struct HasLoad<F, std::void_t<typename F::V>> : std::true_type {};
+constexpr int kAhead = 8;
+
 template <int NV, class F>
 __global__ void __launch_bounds__(kThreads) reduce_kernel(F f, uint64_t count, double* __restrict__ partials) {
   Acc acc[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) acc[v] = {0.0, 0.0};
-  for (uint64_t t = xcd_block(blockIdx.x, gridDim.x) * (uint64_t)kThreads + threadIdx.x; t < count;
-       t += (uint64_t)gridDim.x * kThreads)
-    f(t, acc);
+  const uint64_t step = (uint64_t)gridDim.x * kThreads;
+  uint64_t t = xcd_block(blockIdx.x, gridDim.x) * (uint64_t)kThreads + threadIdx.x;
+  if constexpr (HasLoad<F>::value) {
+    for (; t + (kAhead - 1) * step < count; t += kAhead * step) {
+      typename F::V v[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) v[k] = f.load(t + k * step);
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) f.add(v[k], acc);
+    }
+    for (; t < count; t += step) f.add(f.load(t), acc);
+  } else {
+    for (; t < count; t += step) f(t, acc);
+  }
   __shared__ Acc red[NV][kThreads];
 #pragma unroll
   for (int v = 0; v < NV; ++v) red[v][threadIdx.x] = acc[v];
@@ -71,19 +92,26 @@ __global__ void __launch_bounds__(kThreads) finalize_kernel(const double* __rest
 
 template <class R>
 struct NormF {
+  using V = cplx2<R>;
   const cplx2<R>* psi;
-  __device__ void operator()(uint64_t t, Acc* acc) const {
-    const cplx2<R> v = psi[t];
-    nadd(acc[0], abs2_d(v.a) + abs2_d(v.b));
-  }
+  __device__ V load(uint64_t t) const { return ld_nt(psi + t); }
+  __device__ void add(const V& v, Acc* acc) const { nadd(acc[0], abs2_d(v.a) + abs2_d(v.b)); }
+};
+
+template <class Ra, class Rb>
+struct AmpPair {
+  cplx<Ra> a;
+  cplx<Rb> b;
 };
 
 template <class Ra, class Rb>
 struct OverlapF {
   const cplx<Ra>* a;
   const cplx<Rb>* b;
-  __device__ void operator()(uint64_t t, Acc* acc) const {
-    const double ar = a[t].re, ai = a[t].im, br = b[t].re, bi = b[t].im;
+  using V = AmpPair<Ra, Rb>;
+  __device__ V load(uint64_t t) const { return {ld_nt(a + t), ld_nt(b + t)}; }
+  __device__ void add(const V& v, Acc* acc) const {
+    const double ar = v.a.re, ai = v.a.im, br = v.b.re, bi = v.b.im;
     nadd(acc[0], ar * br + ai * bi);
     nadd(acc[1], ar * bi - ai * br);
   }
@@ -94,10 +122,12 @@ struct DistanceF {
   const cplx<Ra>* a;
   const cplx<Rb>* b;
   double ar, ai, bs;  // || bs * b - (ar + i ai) * a ||^2
-  __device__ void operator()(uint64_t t, Acc* acc) const {
-    const double xr = a[t].re, xi = a[t].im;
-    const double dr = bs * (double)b[t].re - (ar * xr - ai * xi);
-    const double di = bs * (double)b[t].im - (ar * xi + ai * xr);
+  using V = AmpPair<Ra, Rb>;
+  __device__ V load(uint64_t t) const { return {ld_nt(a + t), ld_nt(b + t)}; }
+  __device__ void add(const V& v, Acc* acc) const {
+    const double xr = v.a.re, xi = v.a.im;
+    const double dr = bs * (double)v.b.re - (ar * xr - ai * xi);
+    const double di = bs * (double)v.b.im - (ar * xi + ai * xr);
     nadd(acc[0], dr * dr + di * di);
   }
 };

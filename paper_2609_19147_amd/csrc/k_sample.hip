@@ -11,6 +11,7 @@
 // wavefront per sample searches the block prefixes, scans the block's
 // sub-block sums and finally the sub-block's 64 probabilities.
 #include "kernels.h"
+#include "lanes.h"
 
 #include <mutex>
 #include <string>
@@ -41,34 +42,50 @@ __device__ __forceinline__ double wave_scan(double x, uint32_t lane) {
   }
   return x;
 }
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
-  return x;
-}
-
-// sub[s] = sum of the probabilities of amplitudes [s sub_len, (s + 1) sub_len),
-// sub_len <= 64, one wavefront per sub-block.
+// One workgroup per block: sub[s] = the probability of sub-block s (sub_len <=
+// 64 amplitudes, one per lane), blk[b] = the sum of the block's sub-block sums
+// in order.  A wavefront takes eight sub-blocks at a time, their loads in
+// flight together and their sums taken four at a time.
+// Bound by the read of the state: 26 qubits complex64, sums of sub-blocks one
+// by one through LDS and a second kernel over them 200 us, this one 120 us.
 template <class R>
-__global__ void __launch_bounds__(kSampThreads) sub_sums_kernel(const cplx<R>* __restrict__ psi, uint64_t n_sub,
-                                                                uint32_t sub_len, double* __restrict__ sub) {
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint64_t waves = (uint64_t)gridDim.x * (kSampThreads / 64);
-  for (uint64_t s = blockIdx.x * (uint64_t)(kSampThreads / 64) + (threadIdx.x >> 6); s < n_sub; s += waves) {
-    const double p = lane < sub_len ? prob(psi[s * sub_len + lane]) : 0.0;
-    const double t = wave_sum(p);
-    if (lane == 0) sub[s] = t;
-  }
-}
-
-// blk[b] = sum of its subs_per_block sub-block sums, in order.
-__global__ void __launch_bounds__(kSampThreads) block_sums_kernel(const double* __restrict__ sub, uint64_t n_blk,
-                                                                  uint32_t subs_per_block, double* __restrict__ blk) {
-  for (uint64_t b = blockIdx.x * (uint64_t)kSampThreads + threadIdx.x; b < n_blk;
-       b += (uint64_t)gridDim.x * kSampThreads) {
-    double t = 0.0;
-    for (uint32_t j = 0; j < subs_per_block; ++j) t += sub[b * subs_per_block + j];
-    blk[b] = t;
+__global__ void __launch_bounds__(kSampThreads) block_masses_kernel(const cplx<R>* __restrict__ psi, uint64_t n_blk,
+                                                                    uint32_t subs_per_block, uint32_t sub_len,
+                                                                    double* __restrict__ sub, double* __restrict__ blk) {
+  __shared__ double s_sub[256];
+  constexpr uint32_t kWaves = kSampThreads / 64, kU = 8;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  for (uint64_t b = blockIdx.x; b < n_blk; b += gridDim.x) {
+    const uint64_t s0 = b * subs_per_block;
+    for (uint32_t j = wave * kU; j < subs_per_block; j += kWaves * kU) {
+      cplx<R> a[kU];
+#pragma unroll
+      for (uint32_t k = 0; k < kU; ++k) {
+        a[k] = cplx<R>{R(0), R(0)};
+        if (j + k < subs_per_block && lane < sub_len) a[k] = ld_nt(psi + (s0 + j + k) * sub_len + lane);
+      }
+#pragma unroll
+      for (uint32_t h = 0; h < kU; h += 4) {
+        const double p[4] = {prob(a[h]), prob(a[h + 1]), prob(a[h + 2]), prob(a[h + 3])};
+        const double t = wave_sum4(p);
+        const uint32_t o = j + h + wave_sum4_value(lane);
+        if ((lane & 15u) == 0 && o < subs_per_block) s_sub[o] = t;
+      }
+    }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < subs_per_block; j += kSampThreads) sub[s0 + j] = s_sub[j];
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (uint32_t j0 = 0; j0 < subs_per_block; j0 += 16) {
+        double v[16];
+#pragma unroll
+        for (uint32_t k = 0; k < 16; ++k) v[k] = j0 + k < subs_per_block ? s_sub[j0 + k] : 0.0;
+#pragma unroll
+        for (uint32_t k = 0; k < 16; ++k) t += v[k];
+      }
+      blk[b] = t;
+    }
+    __syncthreads();
   }
 }
 
@@ -79,23 +96,44 @@ __global__ void __launch_bounds__(kScanThreads) block_scan_kernel(const double* 
   const uint64_t chunk = (n + kScanThreads - 1) / kScanThreads;
   const uint64_t b0 = threadIdx.x * chunk, b1 = b0 + chunk < n ? b0 + chunk : n;
   double t = 0.0;
-  for (uint64_t b = b0; b < b1; ++b) t += blk[b];
+  for (uint64_t b = b0; b < b1; b += 8) {
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = b + k < b1 ? blk[b + k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t += v[k];
+  }
   tot[threadIdx.x] = t;
   __syncthreads();
   if (threadIdx.x == 0) {
+    // one chain of additions, its operands read 16 ahead
     double run = 0.0;
-    for (int k = 0; k < kScanThreads; ++k) {
-      const double v = tot[k];
-      tot[k] = run;
-      run += v;
+    for (int k0 = 0; k0 < kScanThreads; k0 += 16) {
+      double v[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = tot[k0 + k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double x = v[k];
+        v[k] = run;
+        run += x;
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) tot[k0 + k] = v[k];
     }
     P[n] = run;
   }
   __syncthreads();
   double run = tot[threadIdx.x];
-  for (uint64_t b = b0; b < b1; ++b) {
-    P[b] = run;
-    run += blk[b];
+  for (uint64_t b = b0; b < b1; b += 8) {
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = b + k < b1 ? blk[b + k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (b + k < b1) P[b + k] = run;
+      run += v[k];
+    }
   }
 }
 
@@ -177,42 +215,80 @@ __global__ void __launch_bounds__(kSampThreads) sample_kernel(const cplx<R>* __r
   if (lane == 0) out[k] = base + idx;
 }
 
-// Marginal: out_partial[bin * chunks + c] = sum over the chunk c of the other
-// qubits' index values r of p(compose(bin, r)).
+// Marginal.  Rows of 2^row consecutive amplitudes, one pair per thread: the
+// selected bits below `row` follow from the thread and the pair's half, those
+// above it (hsel) from the workgroup, so reads are whole rows whatever is
+// selected.  Workgroup (hb, c) sums the rows of chunk c of high bin hb, then
+// folds its pairs into the low bins; partial[(hb chunks + c) 2^kl + lb].
+// Bound by the read of the state: 26 qubits, 8 of them selected, 168 us with
+// an index deposit per amplitude, 91 us.
 template <class R>
 __global__ void __launch_bounds__(kSampThreads) marginal_kernel(const cplx<R>* __restrict__ psi, MarginalArgs A,
                                                                 double* __restrict__ partials) {
-  const uint32_t bin = blockIdx.x / A.chunks, c = blockIdx.x % A.chunks;
-  uint64_t bpart = 0;
-  for (uint32_t j = 0; j < A.k; ++j)
-    if ((bin >> j) & 1u) bpart |= 1ull << A.sel[j];
-  const uint64_t r0 = (uint64_t)c * A.chunk_len, r1 = r0 + A.chunk_len;
-  double s = 0.0;
-  for (uint64_t r = r0 + threadIdx.x; r < r1; r += kSampThreads) {
-    uint64_t i = r;
-    for (uint32_t j = 0; j < A.k; ++j) {  // ascending: open a zero at every selected bit
-      const uint64_t lo = i & ((1ull << A.sel[j]) - 1ull);
-      i = ((i >> A.sel[j]) << (A.sel[j] + 1)) | lo;
+  __shared__ double red[2 * kSampThreads];
+  const uint32_t hb = blockIdx.x / A.chunks, c = blockIdx.x % A.chunks;
+  const bool active = 2u * threadIdx.x < (1u << A.row);
+  // state index bits above the row, selected ones fixed to hb's, the others
+  // counting: (i | hsel) + 2^row carries over the selected bits
+  uint32_t fixed = 0, i = 0;
+  for (uint32_t j = 0, m = A.hsel; m; ++j, m &= m - 1u)
+    if ((hb >> j) & 1u) fixed |= m & (0u - m);
+  for (uint32_t j = 0, m = A.hfree; m; ++j, m &= m - 1u)
+    if (((uint64_t)c * A.chunk_rows >> j) & 1u) i |= m & (0u - m);
+  double s0 = 0.0, s1 = 0.0;
+  constexpr uint32_t kU = 8;
+  const cplx2<R>* p2 = reinterpret_cast<const cplx2<R>*>(psi) + threadIdx.x;
+  if (active) {
+    for (uint32_t r = 0; r < A.chunk_rows; r += kU) {
+      cplx2<R> v[kU];
+#pragma unroll
+      for (uint32_t k = 0; k < kU; ++k) {
+        v[k] = cplx2<R>{{R(0), R(0)}, {R(0), R(0)}};
+        if (r + k < A.chunk_rows) {
+          v[k] = ld_nt(p2 + ((i | fixed) >> 1));
+          i = ((i | ~A.hfree) + 1u) & A.hfree;
+        }
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < kU; ++k) {
+        s0 += prob(v[k].a);
+        s1 += prob(v[k].b);
+      }
     }
-    s += prob(psi[i | bpart]);
   }
-  __shared__ double red[kSampThreads];
-  red[threadIdx.x] = s;
+  red[2 * threadIdx.x] = s0;
+  red[2 * threadIdx.x + 1] = s1;
   __syncthreads();
-  for (int stride = kSampThreads / 2; stride > 0; stride >>= 1) {
-    if ((int)threadIdx.x < stride) red[threadIdx.x] += red[threadIdx.x + stride];
+  // fold the row's unselected bits away, the highest first (a fixed order);
+  // what is left sits at the positions made of selected bits alone
+  const uint32_t rest = ((1u << A.row) - 1u) & ~A.lsel;
+  for (uint32_t bit = 1u << 8, folded = 0; bit; bit >>= 1) {
+    if (!(rest & bit)) continue;
+    folded |= bit;
+    for (uint32_t p = threadIdx.x; p < (1u << A.row); p += kSampThreads)
+      if (!(p & folded)) red[p] += red[p | bit];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
+  const uint32_t kl = (uint32_t)__builtin_popcount(A.lsel);
+  for (uint32_t lb = threadIdx.x; lb < (1u << kl); lb += kSampThreads) {
+    uint32_t at = 0;
+    for (uint32_t j = 0, m = A.lsel; m; ++j, m &= m - 1u)
+      if ((lb >> j) & 1u) at |= m & (0u - m);
+    partials[((size_t)blockIdx.x << kl) + lb] = red[at];
+  }
 }
 
+// One wavefront per bin adds its chunks: lanes strided, then a fixed butterfly.
 __global__ void __launch_bounds__(kSampThreads) marginal_finalize(const double* __restrict__ partials,
-                                                                  uint32_t bins, uint32_t chunks,
+                                                                  uint32_t bins, uint32_t chunks, uint32_t kl,
                                                                   double* __restrict__ out) {
-  for (uint32_t b = blockIdx.x * kSampThreads + threadIdx.x; b < bins; b += gridDim.x * kSampThreads) {
+  const uint32_t lane = threadIdx.x & 63u, waves = gridDim.x * (kSampThreads / 64);
+  for (uint32_t b = blockIdx.x * (kSampThreads / 64) + (threadIdx.x >> 6); b < bins; b += waves) {
+    const double* p = partials + ((size_t)(b >> kl) * chunks << kl) + (b & ((1u << kl) - 1u));
     double t = 0.0;
-    for (uint32_t c = 0; c < chunks; ++c) t += partials[(size_t)b * chunks + c];
-    out[b] = t;
+    for (uint32_t c = lane; c < chunks; c += 64) t += p[(size_t)c << kl];
+    t = wave_sum_fixed(t);
+    if (lane == 0) out[b] = t;
   }
 }
 
@@ -245,10 +321,8 @@ void launch_sample(const cplx<R>* psi, int n, const double* u_dev, uint64_t coun
   double* sub = work;
   double* blk = sub + G.n_sub;
   double* P = blk + G.n_blk;
-  QS_LAUNCH("sample_sub_sums", s, sub_sums_kernel<R>, dim3(grid_of(G.n_sub, kSampThreads / 64, 65536)),
-            dim3(kSampThreads), 0, s, psi, G.n_sub, G.sub_len, sub);
-  QS_LAUNCH("sample_block_sums", s, block_sums_kernel, dim3(grid_of(G.n_blk, kSampThreads, 4096)),
-            dim3(kSampThreads), 0, s, sub, G.n_blk, G.subs_per_block, blk);
+  QS_LAUNCH("sample_masses", s, block_masses_kernel<R>, dim3(grid_of(G.n_blk, 1, 1u << 20)), dim3(kSampThreads), 0, s,
+            psi, G.n_blk, G.subs_per_block, G.sub_len, sub, blk);
   QS_LAUNCH("sample_scan", s, block_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, blk, G.n_blk, P);
   if (count)
     QS_LAUNCH("sample_draw", s, sample_kernel<R>, dim3(grid_of(count, kSampThreads / 64, 1u << 30)),
@@ -261,10 +335,9 @@ void launch_sample(const cplx<R>* psi, int n, const double* u_dev, uint64_t coun
 // process ends): nothing in it needs clearing, since every region is written
 // before it is read within a call.  Calls that overlap on one GPU share it.
 namespace {
-constexpr size_t kNaNormDoubles = 2 * (size_t)kRedBlocks + 8;
 constexpr size_t kNaSumDoubles = ((size_t)1 << (kNoAllocSampleMaxQubits - 6)) +
                                  2 * ((size_t)1 << (kNoAllocSampleMaxQubits - 14)) + 1;
-constexpr size_t kNaDoubles = kNaNormDoubles + kNaSumDoubles + 2 * kNoAllocSampleMaxDraws;
+constexpr size_t kNaDoubles = kNaSumDoubles + 2 * kNoAllocSampleMaxDraws;
 constexpr int kNaMaxDevices = 64;
 std::mutex g_na_mu;
 double* g_na_ptr[kNaMaxDevices] = {};
@@ -291,9 +364,7 @@ NoAllocSampleScratch noalloc_sample_scratch(int device) {
     base = g_na_ptr[device];
   }
   NoAllocSampleScratch S;
-  S.norm_partials = base;
-  S.norm_out = base + 2 * (size_t)kRedBlocks;
-  S.sums = base + kNaNormDoubles;
+  S.sums = base;
   S.u = S.sums + kNaSumDoubles;
   S.out = (uint64_t*)(S.u + kNoAllocSampleMaxDraws);
   return S;
@@ -304,25 +375,29 @@ size_t marginal_partials(const MarginalArgs& A) { return ((size_t)1 << A.k) * A.
 MarginalArgs marginal_geometry(int n, const int* sel_bits, int k) {
   MarginalArgs A{};
   A.k = (uint32_t)k;
-  for (int j = 0; j < k; ++j) A.sel[j] = (uint32_t)sel_bits[j];
-  const uint64_t rest = 1ull << (n - k);
-  const uint32_t bins = 1u << k;
-  // about 4096 workgroups in all, chunks of at least 4096 index values
-  uint64_t chunks = 4096 / bins;
-  if (chunks < 1) chunks = 1;
-  while (chunks > 1 && rest / chunks < 4096) chunks >>= 1;
-  if (chunks > rest) chunks = rest;
-  A.chunks = (uint32_t)chunks;
-  A.chunk_len = rest / chunks;
+  A.row = (uint32_t)(n < 9 ? n : 9);  // 2 kSampThreads amplitudes
+  uint32_t sel = 0;
+  for (int j = 0; j < k; ++j) sel |= 1u << sel_bits[j];
+  const uint32_t row_mask = (1u << A.row) - 1u, all = n >= 32 ? 0xffffffffu : (1u << n) - 1u;
+  A.lsel = sel & row_mask;
+  A.hsel = sel & ~row_mask;
+  A.hfree = all & ~row_mask & ~sel;
+  const uint32_t rows = 1u << __builtin_popcount(A.hfree), hbins = 1u << __builtin_popcount(A.hsel);
+  // about 4096 workgroups in all, at least eight rows (the loads in flight) each
+  uint32_t chunks = hbins < 4096u ? 4096u / hbins : 1u;
+  while (chunks > 1 && rows / chunks < 8) chunks >>= 1;
+  A.chunks = chunks;
+  A.chunk_rows = rows / chunks;
   return A;
 }
 
 template <class R>
 void launch_marginal(const cplx<R>* psi, const MarginalArgs& A, double* partials, double* out, hipStream_t s) {
-  const uint32_t bins = 1u << A.k;
-  QS_LAUNCH("marginal", s, marginal_kernel<R>, dim3(bins * A.chunks), dim3(kSampThreads), 0, s, psi, A, partials);
-  QS_LAUNCH("marginal_finalize", s, marginal_finalize, dim3(grid_of(bins, kSampThreads, 256)), dim3(kSampThreads),
-            0, s, partials, bins, A.chunks, out);
+  const uint32_t bins = 1u << A.k, kl = (uint32_t)__builtin_popcount(A.lsel);
+  QS_LAUNCH("marginal", s, marginal_kernel<R>, dim3((bins >> kl) * A.chunks), dim3(kSampThreads), 0, s, psi, A,
+            partials);
+  QS_LAUNCH("marginal_finalize", s, marginal_finalize, dim3(grid_of(bins, kSampThreads / 64, 4096)),
+            dim3(kSampThreads), 0, s, partials, bins, A.chunks, kl, out);
 }
 
 template void launch_sample<float>(const cplx<float>*, int, const double*, uint64_t, uint64_t*, double*, hipStream_t);

@@ -220,13 +220,11 @@ void launch_sample(const cplx<R>* psi, int n, const double* u_dev, uint64_t coun
 // Allocation-free sampling (qs_sample_noalloc): its scratch is one static
 // device array per GPU, sized for states of up to kNoAllocSampleMaxQubits
 // qubits and kNoAllocSampleMaxDraws draws per call.  Layout (doubles): the
-// norm reduction's partials (2 kRedBlocks) and result (8), the sampling sums
-// of a kNoAllocSampleMaxQubits-qubit state, the uniforms, the drawn indices.
+// sampling sums of a kNoAllocSampleMaxQubits-qubit state, the uniforms, the
+// drawn indices.
 constexpr int kNoAllocSampleMaxQubits = 26;
 constexpr uint64_t kNoAllocSampleMaxDraws = 1ull << 16;
 struct NoAllocSampleScratch {
-  double* norm_partials;
-  double* norm_out;
   double* sums;
   double* u;
   uint64_t* out;
@@ -236,11 +234,11 @@ struct NoAllocSampleScratch {
 // fails.
 NoAllocSampleScratch noalloc_sample_scratch(int device);
 // Marginal over k <= 16 state bits sel[0] < sel[1] < ...: out[bin] (device),
-// bin bit j = state bit sel[j].
+// bin bit j = state bit sel[j].  Rows are the state bits [0, row); lsel, hsel:
+// the selected bits below and above, hfree: the others above (masks).
 struct MarginalArgs {
-  uint32_t k, chunks;
-  uint64_t chunk_len;
-  uint32_t sel[32];
+  uint32_t k, row, chunks, chunk_rows;
+  uint32_t lsel, hsel, hfree;
 };
 MarginalArgs marginal_geometry(int n, const int* sel_bits, int k);
 size_t marginal_partials(const MarginalArgs& A);

@@ -34,8 +34,8 @@ struct qs_state {
   hipStream_t stream = nullptr;
   double* red_partials = nullptr;
   double* red_out = nullptr;
-  double* expect_buf = nullptr;  // term sums and their partials (qs_expect)
-  size_t expect_cap = 0;
+  void* scratch_buf = nullptr;  // read-out scratch: sums, uniforms, results of one call
+  size_t scratch_cap = 0;
   double* norm_part = nullptr;  // per-tile norm partials of a fused apply-and-norm
   uint64_t norm_cap = 0;
   std::vector<PlanGraphEntry> graphs;  // recorded plans, most recent last
@@ -54,7 +54,7 @@ struct qs_state {
   void ensure_other();
   void ensure_red();
   void ensure_norm(uint64_t tiles);
-  double* ensure_expect(size_t doubles);  // waits for the stream to grow it
+  void* ensure_scratch(size_t bytes);  // waits for the stream to grow it
   void* ensure_work_buf(size_t bytes);  // at least `bytes` of device scratch (waits for the stream to grow it)
   void sync();
   ~qs_state();
