@@ -407,6 +407,9 @@ extern "C" qs_status qs_plan_create(int n, const qs_gate* gates, size_t n_gates,
       o.balance_passes = opts->balance_passes;
     }
     int tb = o.max_tile_bits ? o.max_tile_bits : 13;
+    // (parametrised plans keep their passes: which parameters the adjoint sweep can
+    // isolate depends on them)
+    o.auto_tile = o.max_tile_bits == 0 && low == 0 && n_params == 0;
     if (tb < kRoundBits + 1 || tb > kMaxTileBits) fail(QS_EINVAL, "max_tile_bits out of range");
     auto g = normalise_gates(n, gates, n_gates, n_params);
     auto p = std::make_unique<qs_plan>();

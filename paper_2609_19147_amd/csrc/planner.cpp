@@ -782,6 +782,27 @@ Sched make_groups(int n, int tile_bits, int low_bits) {
   return s;
 }
 
+// Tile limit of segments without (forward) QFT stages when the caller sets none.  The
+// passes of a size are about as long as the rounds of one tile (several waves of
+// workgroups, or a single one below 2^21 amplitudes), so the smallest tile that
+// covers the state in as many groups as 2^13 does is the fastest: more and
+// shorter workgroups per compute unit, same passes.  Measured against 13 bits
+// (11 TFIM steps, us, complex64 | complex128): 16 qubits 10 bits 92 against 119 |
+// 140 against 183, 18 qubits 11 bits 102 against 125 | 165 against 206, 20 qubits
+// 12 bits 177 against 199 | 308 against 355, 24 qubits 12 bits 1184 against 1309 |
+// 2614 against 2921, 26 qubits 12 bits 4474 against 4593 | 9881 against 10806.
+// From 23 qubits up 11 bits gain nothing over 12 (shorter runs in the high
+// tiles).  Segments with QFT stages stay at 13 bits (23 qubits: 90 against
+// 108 us, 24: 174 against 179); inverse stages do not (25-qubit phase
+// estimation 699 against 745 us, in complex128 1623 against 1883).
+int fine_tile_bits(int n, int tile_bits) {
+  auto groups = [&](int t) { return n <= t ? 1 : 1 + (n - t + t - 5) / (t - 4); };
+  int t = tile_bits;
+  const int least = n >= 23 ? 12 : 10;
+  while (t > least && n > t - 1 && groups(t - 1) == groups(tile_bits)) --t;
+  return t;
+}
+
 // The gate's matrix (first listed wire = most significant index bit) re-indexed
 // so that index bit u sits on the u-th smallest target bit.
 DenseIR make_dense(const NGate& g, int32_t gi) {
@@ -820,7 +841,11 @@ struct Item {
 class Builder {
  public:
   Builder(PlanIR& P, int tile_bits, int low_bits)
-      : P(P), n(P.n), sched(make_groups(P.n, tile_bits, low_bits)), window(P.n) {}
+      : P(P),
+        n(P.n),
+        wide(make_groups(P.n, tile_bits, low_bits)),
+        fine(make_groups(P.n, P.opt.auto_tile ? fine_tile_bits(P.n, tile_bits) : tile_bits, low_bits)),
+        window(P.n) {}
 
   void run() {
     const auto& G = P.gates;
@@ -892,7 +917,7 @@ class Builder {
   enum Open { NONE, DIAG, WINDOW, PERM, XX, YY };
   PlanIR& P;
   int n;
-  Sched sched;
+  Sched wide, fine;  // tile groups of segments with and without (forward) QFT stages
   Open open = NONE;
   std::vector<int> diag, perm, pp;
   std::vector<std::vector<int>> window;
@@ -1161,6 +1186,10 @@ class Builder {
     cancel_butterfly_pairs();
     if (seg.empty()) return;
     size_t N = seg.size();
+    bool qft = false;
+    for (const Item& it : seg)
+      qft = qft || (it.ir.type == 0 && P.ops[it.ir.index].kind == OP_QFT);
+    const Sched& sched = qft ? wide : fine;
     std::vector<std::vector<int>> deps(N);
     for (size_t j = 0; j < N; ++j)
       for (size_t i = 0; i < j; ++i) {
@@ -1174,7 +1203,7 @@ class Builder {
       std::vector<int> best_list;
       for (size_t g = 0; g < sched.grp.size(); ++g) {
         std::vector<int> list;
-        int ops = scan(g, deps, done, list);
+        int ops = scan_mask(sched.gmask[g], deps, done, list);
         if (ops > best_ops) { best_ops = ops; best = (int)g; best_list = list; }
       }
       if (best_ops <= 0) {
@@ -1217,11 +1246,6 @@ class Builder {
       P.passes.push_back(std::move(T));
     }
     seg.clear();
-  }
-
-  int scan(size_t g, const std::vector<std::vector<int>>& deps, const std::vector<char>& done,
-           std::vector<int>& list) {
-    return scan_mask(sched.gmask[g], deps, done, list);
   }
 
   // Every ready item in stream order whose written bits lie in the tile mask

@@ -129,7 +129,8 @@ struct LayerIR {
 
 struct PlanOptions {
   int mode = QS_FUSED;
-  int max_tile_bits = 0;  // 0 = default by dtype at apply time
+  int max_tile_bits = 0;  // 0 = default (the planner picks the tiles of each segment)
+  bool auto_tile = false; // set with that default
   int dense_k_max = 6;    // largest UNITARY gate run as a dense block (< 4: none)
   int window_k = 5;       // dense-window fusion: largest window (< 4: off)
   int coset_order = 0;    // tile passes' workgroup -> coset order: 0 by geometry,
