@@ -67,7 +67,7 @@ __device__ __forceinline__ uint32_t dense_lds_off(uint32_t pos) { return pos + (
 template <class R, int K>
 constexpr int dense_io() { return K == 16 ? 2 : 4; }
 
-template <class R, int kIO, uint32_t NT = kDenseThreads>
+template <bool kKeep, class R, int kIO, uint32_t NT = kDenseThreads>
 __device__ __forceinline__ void dense_load(const cplx<R>* __restrict__ psi, cplx<R>* T, uint32_t M, uint32_t base,
                                            uint32_t L, const uint32_t* hi_tab) {
   const uint32_t Lmask = (1u << L) - 1u, step = 2u * NT;
@@ -76,7 +76,7 @@ __device__ __forceinline__ void dense_load(const cplx<R>* __restrict__ psi, cplx
 #pragma unroll
     for (int k = 0; k < kIO; ++k) {
       const uint32_t p = p0 + step * k;
-      if (p < M) v[k] = ld_nt(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
+      if (p < M) v[k] = ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
     }
 #pragma unroll
     for (int k = 0; k < kIO; ++k) {
@@ -86,7 +86,7 @@ __device__ __forceinline__ void dense_load(const cplx<R>* __restrict__ psi, cplx
   }
 }
 
-template <class R, int kIO, uint32_t NT = kDenseThreads>
+template <bool kKeep, class R, int kIO, uint32_t NT = kDenseThreads>
 __device__ __forceinline__ void dense_store(cplx<R>* __restrict__ psi, const cplx<R>* T, uint32_t M, uint32_t base,
                                             uint32_t L, const uint32_t* hi_tab) {
   const uint32_t Lmask = (1u << L) - 1u, step = 2u * NT;
@@ -107,14 +107,14 @@ __device__ __forceinline__ void dense_store(cplx<R>* __restrict__ psi, const cpl
 
 // Accesses [K0, K1) of a tile's pair accesses (p = 2 threadIdx.x + 2 NT k, NT
 // threads) into registers, and from registers into the LDS tile.
-template <class R, int K0, int K1, uint32_t NT = kDenseThreads>
+template <bool kKeep, class R, int K0, int K1, uint32_t NT = kDenseThreads>
 __device__ __forceinline__ void dense_issue(const cplx<R>* __restrict__ psi, uint32_t base, uint32_t L,
                                             const uint32_t* hi_tab, cplx2<R>* v) {
   const uint32_t Lmask = (1u << L) - 1u;
 #pragma unroll
   for (int k = K0; k < K1; ++k) {
     const uint32_t p = 2u * threadIdx.x + 2u * NT * k;
-    v[k - K0] = ld_nt(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
+    v[k - K0] = ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
   }
 }
 template <class R, int K0, int K1, uint32_t NT = kDenseThreads>
@@ -127,6 +127,7 @@ __device__ __forceinline__ void dense_put(cplx<R>* T, const cplx2<R>* v) {
 }
 
 // complex128 k = 4: one 16-byte amplitude per lane and access.
+template <bool kKeep>
 __device__ __forceinline__ void dense_load1(const cplx<double>* __restrict__ psi, cplx<double>* T, uint32_t M,
                                             uint32_t base, uint32_t L, const uint32_t* hi_tab) {
   constexpr int kIO = 8;
@@ -136,7 +137,7 @@ __device__ __forceinline__ void dense_load1(const cplx<double>* __restrict__ psi
 #pragma unroll
     for (int k = 0; k < kIO; ++k) {
       const uint32_t p = p0 + kDenseThreads * k;
-      if (p < M) v[k] = ld_nt(psi + (base | (p & Lmask) | hi_tab[p >> L]));
+      if (p < M) v[k] = ld_state<kKeep>(psi + (base | (p & Lmask) | hi_tab[p >> L]));
     }
 #pragma unroll
     for (int k = 0; k < kIO; ++k) {
@@ -145,6 +146,7 @@ __device__ __forceinline__ void dense_load1(const cplx<double>* __restrict__ psi
     }
   }
 }
+template <bool kKeep>
 __device__ __forceinline__ void dense_store1(cplx<double>* __restrict__ psi, const cplx<double>* T, uint32_t M,
                                              uint32_t base, uint32_t L, const uint32_t* hi_tab) {
   constexpr int kIO = 8;
@@ -244,8 +246,12 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     return base;
   };
   cplx2<R> pre[kPipe ? kPre : 1];
+  auto issue_pre = [&](uint32_t base) {
+    if (G.keep) dense_issue<true, R, 0, kPre>(psi, base, G.L, hi_tab, pre);
+    else dense_issue<false, R, 0, kPre>(psi, base, G.L, hi_tab, pre);
+  };
   if constexpr (kPipe) {
-    if (pipe && blockIdx.x < G.n_tiles) dense_issue<R, 0, kPre>(psi, tile_base(blockIdx.x), G.L, hi_tab, pre);
+    if (pipe && blockIdx.x < G.n_tiles) issue_pre(tile_base(blockIdx.x));
   }
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
     // coset bits of tile t (the state bits outside the tile)
@@ -254,7 +260,8 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     if (kPipe && pipe) {
       if constexpr (kPre < kAcc) {
         cplx2<R> rest[kAcc > kPre ? kAcc - kPre : 1];
-        dense_issue<R, kPre, kAcc>(psi, base, G.L, hi_tab, rest);
+        if (G.keep) dense_issue<true, R, kPre, kAcc>(psi, base, G.L, hi_tab, rest);
+        else dense_issue<false, R, kPre, kAcc>(psi, base, G.L, hi_tab, rest);
         dense_put<R, 0, kPre>(T, pre);
         dense_put<R, kPre, kAcc>(T, rest);
       } else {
@@ -263,14 +270,16 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     } else if constexpr (sizeof(R) == 8 && K == 16) {
       // complex128, k = 4 (K = 16, memory-bound): one 16-byte amplitude per lane and
       // access (for k = 5 the extra address work costs more than it saves)
-      dense_load1(psi, T, M, base, G.L, hi_tab);
+      if (G.keep) dense_load1<true>(psi, T, M, base, G.L, hi_tab);
+      else dense_load1<false>(psi, T, M, base, G.L, hi_tab);
     } else {
-      dense_load<R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
+      if (G.keep) dense_load<true, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
+      else dense_load<false, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
     }
     __syncthreads();
     if constexpr (kPipe) {
       if (pipe && t + gridDim.x < G.n_tiles)
-        dense_issue<R, 0, kPre>(psi, tile_base(t + gridDim.x), G.L, hi_tab, pre);
+        issue_pre(tile_base(t + gridDim.x));
     }
 
     // uniform trip count: with split row tiles the two waves of a pair read
@@ -311,9 +320,11 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     }
     __syncthreads();
     if constexpr (sizeof(R) == 8 && K == 16) {
-      dense_store1(psi, T, M, base, G.L, hi_tab);
+      if (G.keep) dense_store1<true>(psi, T, M, base, G.L, hi_tab);
+      else dense_store1<false>(psi, T, M, base, G.L, hi_tab);
     } else {
-      dense_store<R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
+      if (G.keep) dense_store<true, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
+      else dense_store<false, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
     }
     __syncthreads();
   }
@@ -375,16 +386,21 @@ __global__ void __launch_bounds__(kThreads6) dense_kernel_k6_c128(cplx<double>* 
     return base;
   };
   cplx2<double> pre[kAcc];
-  if (pipe && blockIdx.x < G.n_tiles) dense_issue<double, 0, kAcc, NT>(psi, tile_base(blockIdx.x), G.L, hi_tab, pre);
+  auto issue_pre = [&](uint32_t base) {
+    if (G.keep) dense_issue<true, double, 0, kAcc, NT>(psi, base, G.L, hi_tab, pre);
+    else dense_issue<false, double, 0, kAcc, NT>(psi, base, G.L, hi_tab, pre);
+  };
+  if (pipe && blockIdx.x < G.n_tiles) issue_pre(tile_base(blockIdx.x));
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
     const uint32_t base = tile_base(t);
     if (pipe)
       dense_put<double, 0, kAcc, NT>(T, pre);
     else
-      dense_load<double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+      if (G.keep) dense_load<true, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+      else dense_load<false, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
     __syncthreads();
     if (pipe && t + gridDim.x < G.n_tiles)
-      dense_issue<double, 0, kAcc, NT>(psi, tile_base(t + gridDim.x), G.L, hi_tab, pre);
+      issue_pre(tile_base(t + gridDim.x));
     for (uint32_t it = 0; it < trips; ++it) {
       const uint32_t cb = cb0 + it * cbs;
       const bool active = cb < ncb;
@@ -419,7 +435,8 @@ __global__ void __launch_bounds__(kThreads6) dense_kernel_k6_c128(cplx<double>* 
       }
     }
     __syncthreads();
-    dense_store<double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+    if (G.keep) dense_store<true, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+    else dense_store<false, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
     __syncthreads();
   }
 }
@@ -466,7 +483,10 @@ DenseGeom dense_geometry(int n, int k, const int* bits_sorted) {
 template <class R>
 bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx<R>* U_dev, hipStream_t s) {
   if (!dense_supported(n, k, sizeof(R) == 8)) return false;
-  const DenseGeom G = dense_geometry(n, k, bits_sorted);
+  DenseGeom G = dense_geometry(n, k, bits_sorted);
+  // cached reads, streamed writes (a ladder's 24-qubit window passes 65 against
+  // 71 us; cached writes 81, the tiles' short runs evicting each other)
+  G.keep = keep_resident(sizeof(cplx<R>) << n);
   const uint32_t M = 1u << G.m;
   const size_t lds = sizeof(cplx<R>) * (M + ((M >> 5) << 1)) + 64 * sizeof(uint32_t);
   const uint32_t grid = G.n_tiles < 2048u ? G.n_tiles : 2048u;

@@ -485,6 +485,7 @@ __device__ __forceinline__ Ctx coset_ctx(const TileKArgs<R>& A, uint32_t coset) 
 // complex128: one 16-byte amplitude per lane and access, consecutive lanes on
 // consecutive amplitudes (a pair per lane would be two 16-byte accesses at a
 // 32-byte lane stride, each half-filling its requests)
+template <bool kKeep>
 __device__ __forceinline__ void tile_load_c128(const TileKArgs<double>& A, const Ctx& C, cplx<double>* T) {
   const uint32_t M = 1u << A.m, nthr = blockDim.x;
   const cplx<double>* __restrict__ psi = A.psi;
@@ -494,7 +495,7 @@ __device__ __forceinline__ void tile_load_c128(const TileKArgs<double>& A, const
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const uint32_t pos = p0 + nthr * k;
-      if (pos < M) v[k] = ld_nt(psi + (C.base | C.dep(pos)));
+      if (pos < M) v[k] = ld_state<kKeep>(psi + (C.base | C.dep(pos)));
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -504,7 +505,7 @@ __device__ __forceinline__ void tile_load_c128(const TileKArgs<double>& A, const
   }
 }
 
-template <class R>
+template <class R, bool kKeep = false>
 __device__ __forceinline__ void tile_load(const TileKArgs<R>& A, const Ctx& C, cplx<R>* T) {
   const uint32_t M = 1u << A.m, stride = 2 * blockDim.x;
   if (A.init_amp != 0.0) {
@@ -514,7 +515,7 @@ __device__ __forceinline__ void tile_load(const TileKArgs<R>& A, const Ctx& C, c
     return;
   }
   if constexpr (sizeof(R) == 8) {
-    tile_load_c128(A, C, T);
+    tile_load_c128<kKeep>(A, C, T);
     return;
   }
   const cplx<R>* __restrict__ psi = A.psi;
@@ -523,16 +524,16 @@ __device__ __forceinline__ void tile_load(const TileKArgs<R>& A, const Ctx& C, c
       cplx2<R> v[kChunk];
 #pragma unroll
       for (int k = 0; k < kChunk; ++k)
-        v[k] = ld_nt(reinterpret_cast<const cplx2<R>*>(psi + (C.base | C.dep(p0 + stride * k))));
+        v[k] = ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (C.base | C.dep(p0 + stride * k))));
 #pragma unroll
       for (int k = 0; k < kChunk; ++k) *reinterpret_cast<cplx2<R>*>(T + lds_off(p0 + stride * k)) = v[k];
     }
   } else {
     for (uint32_t pos = 2 * threadIdx.x; pos < M; pos += stride)
-      *reinterpret_cast<cplx2<R>*>(T + lds_off(pos)) = ld_nt(reinterpret_cast<const cplx2<R>*>(psi + (C.base | C.dep(pos))));
+      *reinterpret_cast<cplx2<R>*>(T + lds_off(pos)) =
+          ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (C.base | C.dep(pos))));
   }
 }
-
 // kTwo: the rounds run on T and T1 together (RoundLoop2).
 template <class R, bool kDiag, bool kTwo = false>
 __device__ __forceinline__ void tile_rounds(const TileKArgs<R>& A, const Ctx& C, cplx<R>* T, uint32_t nthr,
@@ -687,7 +688,7 @@ __device__ __forceinline__ void tile_rounds(const TileKArgs<R>& A, const Ctx& C,
 
 // Stores the tile; returns this thread's FP64 sum of |psi|^2 over what it
 // stored when the pass reports its norm (0 otherwise).
-template <class R>
+template <class R, bool kKeep = false>
 __device__ __forceinline__ double tile_store(const TileKArgs<R>& A, const Ctx& C, const cplx<R>* T, uint32_t nthr) {
   // threads [0, nthr) store the tile
   const uint32_t M = 1u << A.m, stride = 2 * nthr;
@@ -711,7 +712,7 @@ __device__ __forceinline__ double tile_store(const TileKArgs<R>& A, const Ctx& C
         const uint32_t pos = p0 + nthr * k;
         if (pos < M) {
           if (do_scale) v[k] = cscale(v[k], sc);
-          st_nt(psi + (C.base | C.dep(pos)), v[k]);
+          st_state<kKeep>(psi + (C.base | C.dep(pos)), v[k]);
           if (A.norm_part != nullptr) nacc += abs2_d(v[k]);
         }
       }
@@ -732,7 +733,7 @@ __device__ __forceinline__ double tile_store(const TileKArgs<R>& A, const Ctx& C
       }
 #pragma unroll
       for (int k = 0; k < kChunk; ++k)
-        st_nt(reinterpret_cast<cplx2<R>*>(psi + (C.base | C.dep(p0 + stride * k))), v[k]);
+        st_state<kKeep>(reinterpret_cast<cplx2<R>*>(psi + (C.base | C.dep(p0 + stride * k))), v[k]);
       if (A.norm_part != nullptr) {
 #pragma unroll
         for (int k = 0; k < kChunk; ++k) nacc += abs2_d(v[k].a) + abs2_d(v[k].b);
@@ -745,22 +746,23 @@ __device__ __forceinline__ double tile_store(const TileKArgs<R>& A, const Ctx& C
         v.a = cscale(v.a, sc);
         v.b = cscale(v.b, sc);
       }
-      st_nt(reinterpret_cast<cplx2<R>*>(psi + (C.base | C.dep(pos))), v);
+      st_state<kKeep>(reinterpret_cast<cplx2<R>*>(psi + (C.base | C.dep(pos))), v);
       if (A.norm_part != nullptr) nacc += abs2_d(v.a) + abs2_d(v.b);
     }
   }
   return nacc;
 }
-
-template <class R, bool kDiag>
+// kKeep: cached accesses to the state.  A template parameter: a branch in one
+// kernel cost the streaming passes 1 to 3% (a larger kernel, more scalar spills).
+template <class R, bool kDiag, bool kKeep = false>
 __device__ __forceinline__ void tile_body(const TileKArgs<R>& A, const uint32_t coset) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<R>* T = reinterpret_cast<cplx<R>*>(smem_raw);
   const Ctx C = coset_ctx(A, coset);
-  tile_load<R>(A, C, T);
+  tile_load<R, kKeep>(A, C, T);
   __syncthreads();
   tile_rounds<R, kDiag>(A, C, T, blockDim.x);
-  const double nacc = tile_store<R>(A, C, T, blockDim.x);
+  const double nacc = tile_store<R, kKeep>(A, C, T, blockDim.x);
   if (A.norm_part != nullptr) {
     const double t = block_sum_fixed(nacc);
     if (threadIdx.x == 0) A.norm_part[coset] = t;
@@ -775,10 +777,10 @@ __global__ void __launch_bounds__(kMaxThreads) tile_kernel(TileKArgs<R> A) {
 // complex64 passes: registers capped at 128 so that four waves fit per SIMD
 // (two 512-thread workgroups of 2^13-amplitude tiles, or four of 2^12, share
 // a CU's LDS).
-template <bool kDiag>
+template <bool kDiag, bool kKeep>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 tile_kernel_c64(TileKArgs<float> A) {
-  tile_body<float, kDiag>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
+  tile_body<float, kDiag, kKeep>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
 }
 
 // ---- software-pipelined tile passes ------------------------------------------
@@ -820,7 +822,6 @@ __device__ __forceinline__ void pipe_issue(const TileKArgs<R>& A, const Ctx& C, 
     v[k - K0] = ld_nt(reinterpret_cast<const E*>(A.psi + (C.base | C.dep(pos))));
   }
 }
-
 template <class R, int K0, int K1>
 __device__ __forceinline__ void pipe_to_lds(const typename PipeAccess<R>::T* v, cplx<R>* T) {
   using E = typename PipeAccess<R>::T;
@@ -890,7 +891,6 @@ __device__ __forceinline__ void ws_issue(const TileKArgs<R>& A, const Ctx& C, ui
     v[k] = ld_nt(reinterpret_cast<const E*>(A.psi + (C.base | C.dep(pos))));
   }
 }
-
 template <class R>
 __device__ __forceinline__ void ws_to_lds(const typename PipeAccess<R>::T* v, uint32_t pt, cplx<R>* T) {
   using E = typename PipeAccess<R>::T;
@@ -1111,14 +1111,14 @@ void launch_tile_k(const TileKArgs<R>& A, hipStream_t s) {
             tile_lds(A.m, sizeof(cplx<R>)), s, A);
 }
 
-template <bool kDiag>
+template <bool kDiag, bool kKeep>
 void launch_tile_c64(const TileKArgs<float>& A, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    allow_dynamic_lds((const void*)tile_kernel_c64<kDiag>, kTileDynLds, "tile_pass");
+    allow_dynamic_lds((const void*)tile_kernel_c64<kDiag, kKeep>, kTileDynLds, "tile_pass");
     attr_set = true;
   }
-  QS_LAUNCH("tile_pass", s, tile_kernel_c64<kDiag>, dim3(1u << (A.n - A.m)), dim3(tile_threads(A.m)),
+  QS_LAUNCH("tile_pass", s, (tile_kernel_c64<kDiag, kKeep>), dim3(1u << (A.n - A.m)), dim3(tile_threads(A.m)),
             tile_lds(A.m, sizeof(cplx<float>)), s, A);
 }
 
@@ -1176,9 +1176,9 @@ void launch_tile(const TileKArgs<R>& A, hipStream_t s) {
   }
   if constexpr (sizeof(R) == 4) {
     if (A.diag != nullptr)
-      launch_tile_c64<true>(A, s);
+      A.keep ? launch_tile_c64<true, true>(A, s) : launch_tile_c64<true, false>(A, s);
     else
-      launch_tile_c64<false>(A, s);
+      A.keep ? launch_tile_c64<false, true>(A, s) : launch_tile_c64<false, false>(A, s);
   } else {
     if (A.diag != nullptr)
       launch_tile_k<R, true>(A, s);

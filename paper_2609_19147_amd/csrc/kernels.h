@@ -66,6 +66,8 @@ struct TileKArgs {
   uint32_t order;     // workgroup -> coset: 0 XCD-blocked (each XCD a contiguous
                       // range of cosets), 1 launch order (concurrent workgroups
                       // of all XCDs on neighbouring cosets)
+  uint32_t keep;      // for the launcher, complex64: 1 cached accesses to psi
+                      // (keep_resident), 0 streaming
 };
 template <class R> void launch_tile(const TileKArgs<R>& A, hipStream_t s);
 // Fused adjoint step (declared here, RhoTileArgs below): the pass A undone on
@@ -124,6 +126,7 @@ struct DenseGeom {
   uint32_t n_free;         // state bits outside the tile (ascending) ...
   uint32_t free_bit[32];
   uint32_t n_tiles;        // 2^n_free
+  uint32_t keep;           // 1: cached accesses to psi (keep_resident)
 };
 bool dense_supported(int n, int k, bool complex128);
 DenseGeom dense_geometry(int n, int k, const int* bits_sorted);

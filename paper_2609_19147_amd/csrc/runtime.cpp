@@ -537,6 +537,13 @@ namespace qs {
 
 namespace {
 
+// complex64 tile passes keep a state resident from 128 MiB: 25 qubits (256 MiB)
+// 13 TFIM passes 1343 against 1506 us, 24 qubits 740 against 807; at 64 MiB the
+// passes are not bound by memory and streaming is 4% faster.  complex128 passes
+// and the adjoint's two states always stream (24 complex128 qubits: Walsh 8%
+// faster resident, Heisenberg 5% slower; two states of 128 MiB 2 to 4% slower).
+constexpr uint64_t kTileResidentFrom = 128ull << 20;
+
 // Coset order of a tile pass (TileKArgs::order).  By geometry: measured at
 // 30 qubits, contiguous tiles stream fastest XCD-blocked, tiles over high
 // bits with runs of 2^5 amplitudes or more in launch order (neighbouring
@@ -572,6 +579,7 @@ TileKArgs<R> tile_args(qs_state& s, qs_plan& p, int pass) {
   A.n_rounds = d.pass_nrounds[pass];
   A.n = s.n;
   A.scale = d.pass_scale[pass];
+  A.keep = keep_resident(s.state_bytes(), kTileResidentFrom);
   return A;
 }
 template TileKArgs<float> tile_args<float>(qs_state&, qs_plan&, int);
