@@ -219,7 +219,7 @@ void run_adjoint(qs_state& psi, qs_plan& p, const qs_pauli* terms, size_t n_term
       A.a = (uint32_t)T.a;
       A.h = (uint32_t)T.h;
       A.m = (uint32_t)(Lr + T.h);
-      tiled = Lr >= 1 && rho_tile_fits(A.m, sizeof(R));
+      tiled = Lr >= 1 && rho_tile_fits(A.m, sizeof(cplx<R>));
       for (int b : bits) {
         const int pos = b < Lr ? b : (b >= T.a && b < T.a + T.h ? Lr + b - T.a : -1);
         if (pos < 0) tiled = false;
