@@ -22,7 +22,7 @@ PROBE = os.path.join(PKG, "ceiling_probe")
 
 SOURCES = ["planner.cpp", "api.cpp", "runtime.cpp", "expect.cpp", "adjoint.cpp", "batch.cpp",
            "k_tile.hip", "k_dense.hip", "k_sample.hip", "k_stream.hip", "k_plain.hip", "k_reduce.hip",
-           "k_expect.hip"]
+           "k_expect.hip", "k_seq.hip"]
 
 ARCH = os.environ.get("QS_OFFLOAD_ARCH", "gfx950")
 # Packed FP32 instructions are kept out of every kernel.

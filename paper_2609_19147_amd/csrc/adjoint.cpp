@@ -80,17 +80,43 @@ void run_adjoint(qs_state& psi, qs_plan& p, const qs_pauli* terms, size_t n_term
   std::stable_sort(ts.begin(), ts.end(), [](const T3& a, const T3& b) { return a.x < b.x; });
 
   const Range range("qs.adjoint");
+  // states of one tile whose parameters all sit in tile passes: the backward
+  // sweep is one launch that reads psi and lambda (k_seq.hip)
+  std::unique_ptr<SeqGrads> seq;
+  std::vector<std::map<int, size_t>> seq_slot(L);  // bit -> offset of its 8 sums
+  size_t seq_res = 0;
+  {
+    const PlanDev& di = inv.device_for(psi.dtype);
+    bool ok = L > 0 && L <= kSeqMaxSteps && di.seq_layer.size() == L && seq_fits(n, sizeof(cplx<R>), true);
+    if (ok) seq = std::make_unique<SeqGrads>();
+    for (size_t j = 0; ok && j < L; ++j) {
+      ok = di.seq_layer[j] != 0;
+      uint32_t bits = 0;
+      for (const GradEntry& e : entries[L - 1 - j]) {
+        ok = ok && e.kind == 0 && inv.ir.layers[j].kind == L_TILE;
+        if (e.kind == 0) bits |= 1u << e.bit;
+      }
+      if (!ok) break;
+      seq->bits[j] = (uint16_t)bits;
+      seq->slot[j] = (uint32_t)seq_res;
+      for (int b = 0; b < n; ++b)
+        if ((bits >> b) & 1u) {
+          seq_slot[L - 1 - j][b] = seq_res;
+          seq_res += 8;
+        }
+      seq->count = (uint32_t)(j + 1);
+    }
+    if (!ok) seq.reset();
+  }
   // forward
   apply_layers(psi, p, 0, L, false);
-  qs_state& phi = work_state(psi, 0);
   qs_state& lam = work_state(psi, 1);
-  copy_state<R>(phi, psi);
+  std::vector<PauliGroup> groups;
+  std::vector<PauliCount> counts;
   {
     // groups of one X mask; within a group each term's sign (-1)^{popcount(j & z)}
     // is 1 - 2 count(j): constants join c0, Z and ZZ terms of equal coefficient
     // share one count (disjoint masks), longer Z strings count their parity
-    std::vector<PauliGroup> groups;
-    std::vector<PauliCount> counts;
     for (size_t t0 = 0; t0 < ts.size();) {
       size_t t1 = t0;
       while (t1 < ts.size() && ts[t1].x == ts[t0].x) ++t1;
@@ -131,7 +157,8 @@ void run_adjoint(qs_state& psi, qs_plan& p, const qs_pauli* terms, size_t n_term
     }
     const size_t gbytes = std::max<size_t>(groups.size(), 1) * sizeof(PauliGroup);
     const size_t kbytes = std::max<size_t>(counts.size(), 1) * sizeof(PauliCount);
-    void* dterms = psi.ensure_work_buf(gbytes + kbytes);
+    // after the tables, the sums of a sequence's sweep and the energy
+    void* dterms = psi.ensure_work_buf(gbytes + kbytes + (seq_res + 2) * sizeof(double));
     PauliGroup* dg = (PauliGroup*)dterms;
     PauliCount* dk = (PauliCount*)((char*)dterms + gbytes);
     if (!groups.empty())
@@ -142,10 +169,38 @@ void run_adjoint(qs_state& psi, qs_plan& p, const qs_pauli* terms, size_t n_term
       check_hip(hipMemcpyAsync(dk, counts.data(), counts.size() * sizeof(PauliCount), hipMemcpyHostToDevice,
                                psi.stream),
                 "hipMemcpyAsync");
-    launch_pauli_apply<R>((const cplx<R>*)phi.cur_ptr(), (cplx<R>*)lam.cur_ptr(), n, dg, (int)groups.size(), dk,
+    launch_pauli_apply<R>((const cplx<R>*)psi.cur_ptr(), (cplx<R>*)lam.cur_ptr(), n, dg, (int)groups.size(), dk,
                           psi.stream);
+    if (seq) {
+      double* res = (double*)((char*)dterms + gbytes + kbytes);
+      psi.ensure_red();
+      launch_overlap<R, R>((const cplx<R>*)psi.cur_ptr(), (const cplx<R>*)lam.cur_ptr(), 1ull << n, psi.red_partials,
+                           res + seq_res, psi.stream);
+      const PlanDev& di = inv.device_for(psi.dtype);
+      launch_seq_dual<R>((const cplx<R>*)psi.cur_ptr(), (const cplx<R>*)lam.cur_ptr(), n,
+                         (const SeqStep<R>*)((const char*)di.blob + di.seq), *seq, di.blob, di.bytes, res, psi.stream);
+      std::vector<double> r(seq_res + 2), g(p.ir.n_params, 0.0);
+      check_hip(hipMemcpyAsync(r.data(), res, r.size() * sizeof(double), hipMemcpyDeviceToHost, psi.stream),
+                "hipMemcpyAsync");
+      psi.sync();
+      *energy = r[seq_res];
+      for (size_t fl = 0; fl < L; ++fl) {
+        const LayerIR& IL = inv.ir.layers[L - 1 - fl];
+        const double sc = IL.kind == L_TILE ? di.pass_scale[IL.index] : 1.0;
+        for (const GradEntry& e : entries[fl]) {
+          const double* q = r.data() + seq_slot[fl].at(e.bit);
+          cd acc = 0;
+          for (int k = 0; k < 4; ++k) acc += e.K[k] * cd(q[2 * k], q[2 * k + 1]);
+          g[e.param] += e.coef * 2.0 * sc * sc * acc.real();
+        }
+      }
+      std::copy(g.begin(), g.end(), grad);
+      return;
+    }
     psi.sync();
   }
+  qs_state& phi = work_state(psi, 0);
+  copy_state<R>(phi, psi);
   *energy = state_overlap(phi, lam).real();
 
   // backward: every reduction writes its own slot of one device array, read

@@ -88,6 +88,36 @@ template <class R>
 void launch_tile_batched(const TileKArgs<R>* descs_dev, uint32_t count, uint32_t n, uint32_t m, bool has_diag,
                          hipStream_t s);
 
+// One layer of a state of a single tile (k_seq.hip): a tile pass over all n bits
+// (n_rounds > 0), or a GF(2) gather out[y] = in[A y ^ cprime], acol[j] = A e_j.
+constexpr int kSeqMaxBits = 13;
+template <class R>
+struct SeqStep {
+  const TileRound* rounds;
+  const TileOp* ops;
+  const cplx<R>* coef;
+  const DiagDev* diag;
+  const int32_t* qtab;
+  double scale;
+  uint32_t n_rounds, cprime;
+  uint32_t acol[kSeqMaxBits + 1];
+};
+// Cross densities wanted from a backward sweep: per step its requested bits and
+// where their sums go (8 doubles each).
+constexpr uint32_t kSeqMaxSteps = 256;
+struct SeqGrads {
+  uint32_t count;
+  uint32_t slot[kSeqMaxSteps];
+  uint16_t bits[kSeqMaxSteps];
+};
+bool seq_fits(int n, size_t amp_bytes, bool dual);
+template <class R>
+void launch_seq(cplx<R>* psi, int n, const SeqStep<R>* steps, uint32_t count, const void* tables, size_t table_bytes,
+                hipStream_t s);
+template <class R>
+void launch_seq_dual(const cplx<R>* phi, const cplx<R>* lam, int n, const SeqStep<R>* steps, const SeqGrads& G,
+                     const void* tables, size_t table_bytes, double* out, hipStream_t s);
+
 // Diagonal observable value(i) = c0 + sum_g w[g] count_g(i) (count terms as in
 // the phase layers), expectation sum_i |psi_i|^2 value(i), for count instances
 // of n qubits at once; out[k] receives instance k's expectation (device).

@@ -198,20 +198,20 @@ __device__ __forceinline__ void rho_chunk(const cplx<R>* P, const cplx<R>* Q, ui
   }
 }
 
-// Every requested bit's eight sums over tiles P (phi) and Q (lambda) of 2^m
+// Every requested bit's (tbit(0), tbit(1), ...) eight sums over tiles P (phi) and Q (lambda) of 2^m
 // amplitudes, in chunks of rho_chunk_bits; partials value-major:
 // partials[(8 bi + v) ntiles + tile].  All threads of the block take part
 // (barriers inside); red holds kRhoMaxWaves x 32 doubles of shared memory.
-template <class R>
-__device__ __forceinline__ void accumulate_tile(const cplx<R>* P, const cplx<R>* Q, uint32_t M, const RhoTileArgs& A,
-                                                double (*red)[32], double* __restrict__ partials, uint32_t tile,
-                                                uint32_t ntiles) {
+template <class R, class B>
+__device__ __forceinline__ void accumulate_bits(const cplx<R>* P, const cplx<R>* Q, uint32_t M, uint32_t nbits,
+                                                const B& tbit, double (*red)[32], double* __restrict__ partials,
+                                                uint32_t tile, uint32_t ntiles) {
   const uint32_t wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
   constexpr uint32_t kB = rho_chunk_bits<R>();
-  for (uint32_t c0 = 0; c0 < A.nbits; c0 += kB) {
-    const int req = (int)min(kB, A.nbits - c0);
+  for (uint32_t c0 = 0; c0 < nbits; c0 += kB) {
+    const int req = (int)min(kB, nbits - c0);
     uint32_t t[4];
-    for (int k = 0; k < req; ++k) t[k] = A.tbit[c0 + k];
+    for (int k = 0; k < req; ++k) t[k] = tbit(c0 + k);
     // spare bits: the lowest tile bits not requested in this chunk
     for (uint32_t b = 0, k = (uint32_t)req; k < kB; ++b) {
       bool used = false;
@@ -232,6 +232,13 @@ __device__ __forceinline__ void accumulate_tile(const cplx<R>* P, const cplx<R>*
     }
     __syncthreads();
   }
+}
+
+template <class R>
+__device__ __forceinline__ void accumulate_tile(const cplx<R>* P, const cplx<R>* Q, uint32_t M, const RhoTileArgs& A,
+                                                double (*red)[32], double* __restrict__ partials, uint32_t tile,
+                                                uint32_t ntiles) {
+  accumulate_bits<R>(P, Q, M, A.nbits, [&](uint32_t k) { return A.tbit[k]; }, red, partials, tile, ntiles);
 }
 
 }  // namespace rho

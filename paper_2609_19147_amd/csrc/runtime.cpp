@@ -346,6 +346,18 @@ void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
     d.dense_mat[i] = b.put(cast<R>(P.denses[i].mat));
     d.dense_mat_dagger[i] = b.put(cast<R>(P.denses[i].mat_dagger));
   }
+  // layers of a state of one tile that can run as a sequence (k_seq.hip)
+  d.seq_layer.clear();
+  if (seq_fits(P.n, 2 * sizeof(R), false)) {
+    bool any = false;
+    for (const LayerIR& L : P.layers) {
+      const bool ok = L.kind == L_GF2 || (L.kind == L_TILE && P.passes[L.index].L == P.n);
+      d.seq_layer.push_back(ok ? 1 : 0);
+      any = any || L.kind == L_TILE;
+    }
+    if (!any) d.seq_layer.clear();
+    if (any) d.seq = b.put(std::vector<SeqStep<R>>(P.layers.size()));
+  }
   b.put(std::vector<double>(2, 0.0));  // never zero bytes
 }
 
@@ -359,6 +371,29 @@ DiagDev diag_dev(const PlanDev& d, const char* base, int i, bool conj) {
   D.theta = (const double*)(base + d.diag_theta[i]);
   D.global = d.diag_global[i];
   return D;
+}
+
+// The sequence steps of a state of one tile, pointing into the blob likewise.
+template <class R>
+void fill_steps(const PlanIR& P, const PlanDev& d, const std::vector<Gf2Args>& gf2, const char* base, Blob& b) {
+  for (size_t li = 0; li < d.seq_layer.size(); ++li) {
+    if (!d.seq_layer[li]) continue;
+    const LayerIR& L = P.layers[li];
+    SeqStep<R> S{};
+    if (L.kind == L_GF2) {
+      S.cprime = gf2[L.index].cprime;
+      for (int j = 0; j < P.n; ++j) S.acol[j] = gf2[L.index].acol[j];
+    } else {
+      S.rounds = (const TileRound*)(base + d.pass_rounds[L.index]);
+      S.ops = (const TileOp*)(base + d.pass_ops[L.index]);
+      S.coef = (const cplx<R>*)(base + d.pass_coef[L.index]);
+      S.diag = d.pass_diag[L.index] ? (const DiagDev*)(base + d.pass_diag[L.index]) : nullptr;
+      S.qtab = (const int32_t*)(base + d.pass_qtab[L.index]);
+      S.scale = d.pass_scale[L.index];
+      S.n_rounds = d.pass_nrounds[L.index];
+    }
+    std::memcpy(b.bytes.data() + d.seq + li * sizeof S, &S, sizeof S);
+  }
 }
 
 // The per-pass diagonal slot arrays, pointing into the blob at device address base.
@@ -396,6 +431,8 @@ const PlanDev& qs_plan::device_for(qs_dtype dt) {
   if (!d.blob) check_hip(hipMalloc(&d.blob, b.bytes.size()), "hipMalloc(plan tables)");
   d.bytes = b.bytes.size();
   fill_slots(ir, d, (const char*)d.blob, b);
+  if (dt == QS_C64) fill_steps<float>(ir, d, gf2, (const char*)d.blob, b);
+  else fill_steps<double>(ir, d, gf2, (const char*)d.blob, b);
   check_hip(hipMemcpy(d.blob, b.bytes.data(), b.bytes.size(), hipMemcpyHostToDevice), "hipMemcpy(plan tables)");
   d.valid = true;
   return d;
@@ -509,6 +546,8 @@ void qs_plan::refresh_device() {
       continue;
     }
     fill_slots(ir, nd, (const char*)d.blob, b);
+    if (k == QS_C64) fill_steps<float>(ir, nd, gf2, (const char*)d.blob, b);
+    else fill_steps<double>(ir, nd, gf2, (const char*)d.blob, b);
     // the staging buffer is free once the previous upload has run
     if (uploads[k]) check_hip(hipEventSynchronize(ready[k]), "hipEventSynchronize");
     if (staging_cap[k] < b.bytes.size()) {
@@ -593,6 +632,19 @@ void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* 
   const char* base = (const char*)d.blob;
   const PlanIR& P = p.ir;
   for (size_t li = first; li < last; ++li) {
+    // a run of two or more layers of a state of one tile is one launch (the last
+    // layer of an apply that reports its norm runs by itself)
+    if (!d.seq_layer.empty()) {
+      const size_t end = norm_last ? last - 1 : last;
+      size_t e = li;
+      while (e < end && d.seq_layer[e]) ++e;
+      if (e - li >= 2) {
+        launch_seq<R>((cplx<R>*)s.cur_ptr(), s.n, (const SeqStep<R>*)(base + d.seq) + li, (uint32_t)(e - li),
+                      d.blob, d.bytes, s.stream);
+        li = e - 1;
+        continue;
+      }
+    }
     const LayerIR& L = P.layers[li];
     switch (L.kind) {
       case L_DIAG:

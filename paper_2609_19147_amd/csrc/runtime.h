@@ -77,6 +77,8 @@ struct PlanDev {
   std::vector<uint32_t> pass_nrounds;  // per pass: device rounds (diagonals as rounds of their own)
   std::vector<double> pass_scale;      // per pass: the store's scale (butterflies, factored rotations)
   std::vector<size_t> dense_mat, dense_mat_dagger;  // per dense block
+  size_t seq = 0;  // states of one tile: SeqStep[layers] (zeroed for layers of other kinds)
+  std::vector<char> seq_layer;  // per layer: it can run in a sequence (empty: none can)
   std::vector<size_t> plain_mat;  // per layer (only dense plain gates), else 0
 };
 

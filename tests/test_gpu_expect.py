@@ -25,6 +25,7 @@ def _terms(n, seed):
 @pytest.mark.parametrize("dtype", ["c64", "c128"])
 @pytest.mark.parametrize("n", [1, 3, 4, 5, 6, 9, 11, 12, 13, 17])
 def test_terms_against_oracle(n, dtype):
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     psi = W.gaussian_state(n, 100 + n)
     if dtype == "c64":
@@ -42,6 +43,7 @@ def test_terms_against_oracle(n, dtype):
 
 @pytest.mark.parametrize("n,count", [(10, 700), (14, 300)])
 def test_more_terms_than_a_set_holds(n, count):
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     rng = np.random.default_rng(count)
     psi = W.gaussian_state(n, 5)

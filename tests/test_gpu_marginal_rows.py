@@ -20,6 +20,7 @@ def _pick(n, which, rng):
 @pytest.mark.parametrize("which", ["low", "high", "mixed", "edge", "none_low", "sixteen"])
 @pytest.mark.parametrize("n", [2, 8, 9, 10, 13, 18])
 def test_marginal_rows(n, which, dtype):
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     rng = np.random.default_rng(n)
     sel = _pick(n, which, rng)
@@ -35,6 +36,7 @@ def test_marginal_rows(n, which, dtype):
 @pytest.mark.parametrize("n", [4, 6, 8, 14, 16])
 def test_scaled_and_massless_states(n):
     """Draws follow |psi|^2 / ||psi||^2 whatever the norm; no mass is an error."""
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     psi = W.gaussian_state(n, n)
     u = np.random.default_rng(n).random(200)
