@@ -12,22 +12,37 @@
 // Tiles: the target bits plus the c lowest non-target bits (the columns).
 // Every tile bit below the c-th non-target bit is in the tile, so the tile's
 // low L >= c bits are the state's low bits and loads/stores move runs of
-// 2^L >= 16 consecutive amplitudes; the remaining tile bits are targets, whose
-// global offsets come from a small LDS table.  A workgroup (4 waves) stages a
-// tile in LDS; wave w takes 16-column blocks w, w + 4, ...; each block's product
-// is 4 real MFMA 16x16x4 chains per 16-row tile of U:
+// 2^L >= 16 consecutive amplitudes; the remaining tile bits are targets.  A
+// workgroup (4 waves) stages a tile in LDS; wave w takes 16-column blocks w,
+// w + 4, ...; each block's product is 4 real MFMA 16x16x4 chains per 16-row tile
+// of U:
 //   Yr += Ur Xr + Ui (-Xi),   Yi += Ur Xi + Ui Xr,
 // with U's fragments held in registers for the whole kernel and X's read from
 // LDS.  Results go back to the same LDS columns (each column block is read and
-// written by one wave only, or, for complex64 k = 6, by one pair of waves that
-// each compute half of its rows, with a barrier between their reads and
-// writes), then the tile is stored.
+// written by one wave only, or, for k = 6, by one pair of waves that each
+// compute half of its rows, with a barrier between their reads and writes), then
+// the tile is stored.
+//
+// What bounds them: HBM, and for k = 6 (complex128 also k = 5) the matrix cores.
+// Address arithmetic is kept off the tile loop (it cost up to a third of it): a
+// thread's state and LDS offsets are a lane part plus uniform parts, held in
+// registers.  us per block at the start of the tile loop's rework, and now:
+//             complex64                      complex128
+//   n      k=4       k=5       k=6       k=4       k=5        k=6
+//   16   5.6 4.7   8.0 6.5  15.2  9.5  6.2 5.2  10.0 7.6   20.4 13.7
+//   22    18  14    29  17    40   23    28  23    45  32     83   51
+//   25    88  73   100  79   157  115   210 183   249 196    454  316
+//   27   426 370   438 355   679  464   865 756   942 809   1646 1227
+// (27 qubits complex64: 2.1 GB moved, 5.8, 6.0 and 4.6 TB/s; a copy of this
+// size reaches 5.65.)
 //
 // Operand layouts of V_MFMA_{F32,F64}_16X16X4 (wave64): A[i][kk] in lane
 // i + 16 kk, B[kk][j] in lane j + 16 kk; D[i][j] in lane j + 16 (i / 4),
 // register i % 4 for F32, and in lane j + 16 (i % 4), register i / 4 for F64
 // (checked by a one-hot probe of both builtins).
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace qs {
 
@@ -59,273 +74,372 @@ __device__ __forceinline__ f64x4 mfma16(double a, double b, f64x4 c) {
 // LDS element of tile position pos (two pad elements every 32).
 __device__ __forceinline__ uint32_t dense_lds_off(uint32_t pos) { return pos + ((pos >> 5) << 1); }
 
-// Tile load and store with kIO 16-byte accesses per thread issued before any
-// is waited for: a loop that waits for each load before the next pays one
-// memory latency per access.  A k-qubit tile (c = 6 column bits) holds
-// 2^(k+6) amplitudes: two pair accesses per thread at k = 4, four at k = 5,
-// eight (in two batches, the matrix fragments filling the registers) at k = 6.
-template <class R, int K>
-constexpr int dense_io() { return K == 16 ? 2 : 4; }
-
-template <bool kKeep, class R, int kIO, uint32_t NT = kDenseThreads>
-__device__ __forceinline__ void dense_load(const cplx<R>* __restrict__ psi, cplx<R>* T, uint32_t M, uint32_t base,
-                                           uint32_t L, const uint32_t* hi_tab) {
-  const uint32_t Lmask = (1u << L) - 1u, step = 2u * NT;
-  for (uint32_t p0 = 2u * threadIdx.x; p0 < M; p0 += step * kIO) {
-    cplx2<R> v[kIO];
+// First state index of tile t: zeros inserted at the tile's bits, [0, L) and
+// hi_bit (ascending).
+__device__ __forceinline__ uint32_t dense_tile_base(uint32_t t, const DenseGeom& G) {
+  uint32_t base = t << G.L;
 #pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + step * k;
-      if (p < M) v[k] = ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
+  for (uint32_t j = 0; j < 6; ++j)
+    if (j < G.n_hi) {
+      const uint32_t b = G.hi_bit[j];
+      base = ((base >> b) << b << 1) | (base & ((1u << b) - 1u));
     }
-#pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + step * k;
-      if (p < M) *reinterpret_cast<cplx2<R>*>(T + dense_lds_off(p)) = v[k];
-    }
-  }
+  return base;
 }
 
-template <bool kKeep, class R, int kIO, uint32_t NT = kDenseThreads>
-__device__ __forceinline__ void dense_store(cplx<R>* __restrict__ psi, const cplx<R>* T, uint32_t M, uint32_t base,
-                                            uint32_t L, const uint32_t* hi_tab) {
-  const uint32_t Lmask = (1u << L) - 1u, step = 2u * NT;
-  for (uint32_t p0 = 2u * threadIdx.x; p0 < M; p0 += step * kIO) {
-    cplx2<R> v[kIO];
+// A thread's kN accesses of W adjacent amplitudes to each tile of at most
+// W NT kN amplitudes: positions W (tid + NT k), modulo the tile where it is
+// smaller (several threads then move the same amplitudes: a branch here would
+// make a wait for the next tile's loads one for this tile's stores as well).
+// The state offset of a position is the thread's part (one pointer for the
+// whole kernel) and a uniform part of k and the tile, so an access costs one
+// address addition.  All of a tile's loads are issued before the first is
+// waited for.
+template <class R, int W, int kN, uint32_t NT>
+struct DenseIO {
+  typedef typename std::conditional<W == 2, cplx2<R>, cplx<R>>::type V;
+  cplx<R>* lane;
+  uint32_t uni[kN];        // state offsets of the uniform parts
+  uint32_t tid_lds, uni_lds[kN];
+  __device__ __forceinline__ static uint32_t offset(uint32_t p, const DenseGeom& G) {
+    uint32_t off = p & ((1u << G.L) - 1u);
 #pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + step * k;
-      if (p < M) v[k] = *reinterpret_cast<const cplx2<R>*>(T + dense_lds_off(p));
-    }
+    for (uint32_t j = 0; j < 6; ++j) off |= ((p >> (G.L + j)) & 1u) << G.hi_bit[j];
+    return off;
+  }
+  __device__ __forceinline__ DenseIO(cplx<R>* psi, const DenseGeom& G) {
+    const uint32_t wrap = (1u << G.m) - 1u;
+    lane = psi + offset((W * threadIdx.x) & wrap, G);
+    tid_lds = dense_lds_off((W * threadIdx.x) & wrap);
 #pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + step * k;
-      if (p < M) st_nt(reinterpret_cast<cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])), v[k]);
+    for (int k = 0; k < kN; ++k) {
+      uni[k] = offset((W * NT * k) & wrap, G);
+      uni_lds[k] = dense_lds_off((W * NT * k) & wrap);
     }
   }
-}
+  template <bool kKeep>
+  __device__ __forceinline__ void issue(uint32_t base, V (&v)[kN]) const {
+#pragma unroll
+    for (int k = 0; k < kN; ++k) v[k] = ld_state<kKeep>(reinterpret_cast<const V*>(lane + (base | uni[k])));
+  }
+  __device__ __forceinline__ void issue(bool keep, uint32_t base, V (&v)[kN]) const {
+    if (keep) issue<true>(base, v);
+    else issue<false>(base, v);
+  }
+  __device__ __forceinline__ void put(cplx<R>* T, const V (&v)[kN]) const {
+#pragma unroll
+    for (int k = 0; k < kN; ++k) *reinterpret_cast<V*>(T + tid_lds + uni_lds[k]) = v[k];
+  }
+  __device__ __forceinline__ void load(bool keep, uint32_t base, cplx<R>* T) const {
+    V v[kN];
+    issue(keep, base, v);
+    put(T, v);
+  }
+  __device__ __forceinline__ void store(uint32_t base, const cplx<R>* T) const {
+    V v[kN];
+#pragma unroll
+    for (int k = 0; k < kN; ++k) v[k] = *reinterpret_cast<const V*>(T + tid_lds + uni_lds[k]);
+#pragma unroll
+    for (int k = 0; k < kN; ++k) st_nt(reinterpret_cast<V*>(lane + (base | uni[k])), v[k]);
+  }
+};
 
-// Accesses [K0, K1) of a tile's pair accesses (p = 2 threadIdx.x + 2 NT k, NT
-// threads) into registers, and from registers into the LDS tile.
-template <bool kKeep, class R, int K0, int K1, uint32_t NT = kDenseThreads>
-__device__ __forceinline__ void dense_issue(const cplx<R>* __restrict__ psi, uint32_t base, uint32_t L,
-                                            const uint32_t* hi_tab, cplx2<R>* v) {
-  const uint32_t Lmask = (1u << L) - 1u;
+// LDS offsets of the single target (row) and column bits, in increasing order;
+// the offset of several bits is their sum.
+struct DenseBits {
+  uint32_t row[6], col[6];
+  __device__ __forceinline__ explicit DenseBits(const DenseGeom& G) {
+    uint32_t r = G.rowmask, c = ((1u << G.m) - 1u) & ~G.rowmask;
 #pragma unroll
-  for (int k = K0; k < K1; ++k) {
-    const uint32_t p = 2u * threadIdx.x + 2u * NT * k;
-    v[k - K0] = ld_state<kKeep>(reinterpret_cast<const cplx2<R>*>(psi + (base | (p & Lmask) | hi_tab[p >> L])));
-  }
-}
-template <class R, int K0, int K1, uint32_t NT = kDenseThreads>
-__device__ __forceinline__ void dense_put(cplx<R>* T, const cplx2<R>* v) {
-#pragma unroll
-  for (int k = K0; k < K1; ++k) {
-    const uint32_t p = 2u * threadIdx.x + 2u * NT * k;
-    *reinterpret_cast<cplx2<R>*>(T + dense_lds_off(p)) = v[k - K0];
-  }
-}
-
-// complex128 k = 4: one 16-byte amplitude per lane and access.
-template <bool kKeep>
-__device__ __forceinline__ void dense_load1(const cplx<double>* __restrict__ psi, cplx<double>* T, uint32_t M,
-                                            uint32_t base, uint32_t L, const uint32_t* hi_tab) {
-  constexpr int kIO = 8;
-  const uint32_t Lmask = (1u << L) - 1u;
-  for (uint32_t p0 = threadIdx.x; p0 < M; p0 += kDenseThreads * kIO) {
-    cplx<double> v[kIO];
-#pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + kDenseThreads * k;
-      if (p < M) v[k] = ld_state<kKeep>(psi + (base | (p & Lmask) | hi_tab[p >> L]));
-    }
-#pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + kDenseThreads * k;
-      if (p < M) T[dense_lds_off(p)] = v[k];
+    for (int j = 0; j < 6; ++j) {
+      row[j] = dense_lds_off(r & (0u - r));
+      r &= r - 1u;
+      col[j] = dense_lds_off(c & (0u - c));
+      c &= c - 1u;
     }
   }
-}
-template <bool kKeep>
-__device__ __forceinline__ void dense_store1(cplx<double>* __restrict__ psi, const cplx<double>* T, uint32_t M,
-                                             uint32_t base, uint32_t L, const uint32_t* hi_tab) {
-  constexpr int kIO = 8;
-  const uint32_t Lmask = (1u << L) - 1u;
-  for (uint32_t p0 = threadIdx.x; p0 < M; p0 += kDenseThreads * kIO) {
-    cplx<double> v[kIO];
+  // row bits from `at` on of v < 2^nb
+  __device__ __forceinline__ uint32_t rows(uint32_t v, int at, int nb) const {
+    uint32_t o = 0;
 #pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + kDenseThreads * k;
-      if (p < M) v[k] = T[dense_lds_off(p)];
-    }
+    for (int j = 0; j < nb; ++j) o += (v >> j) & 1u ? row[at + j] : 0u;
+    return o;
+  }
+  // column 16 cb + li: a lane's part and a uniform one
+  __device__ __forceinline__ uint32_t col_lane(uint32_t li) const {
+    uint32_t o = 0;
 #pragma unroll
-    for (int k = 0; k < kIO; ++k) {
-      const uint32_t p = p0 + kDenseThreads * k;
-      if (p < M) st_nt(psi + (base | (p & Lmask) | hi_tab[p >> L]), v[k]);
-    }
+    for (int j = 0; j < 4; ++j) o += (li >> j) & 1u ? col[j] : 0u;
+    return o;
   }
-}
-
-// Deposit the low bits of v into the set bits of mask, in increasing order.
-__device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask) {
-  uint32_t r = 0;
-  while (mask) {
-    const uint32_t low = mask & (0u - mask);
-    if (v & 1u) r |= low;
-    v >>= 1;
-    mask &= mask - 1u;
+  __device__ __forceinline__ uint32_t col_block(uint32_t cb) const {
+    return (cb & 1u ? col[4] : 0u) + (cb & 2u ? col[5] : 0u);
   }
-  return r;
-}
+};
 
 template <class R, int K>
-__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(3))) dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_,
-                                                              DenseGeom G) {
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(3)))
+dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_, DenseGeom G) {
   constexpr int KS = K / 4;   // 4-deep steps of the contraction
-  // 16-row tiles of U per wave: complex64 k = 6 splits its four between the
-  // two waves of a pair (each wave holds half of U's fragments, so three
-  // waves fit per SIMD); the pair's waves take the same column blocks
-  constexpr bool kSplit = sizeof(R) == 4 && K == 64;
-  constexpr int RT = kSplit ? 2 : K / 16;
+  constexpr int RT = K / 16;  // 16-row tiles of U
   typedef typename Acc4<R>::T acc_t;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const uint32_t M = 1u << G.m;
   cplx<R>* T = reinterpret_cast<cplx<R>*>(smem_raw);
-  uint32_t* hi_tab = reinterpret_cast<uint32_t*>(smem_raw + sizeof(cplx<R>) * dense_lds_off(M));
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t li = lane & 15u, lk = lane >> 4;
-  const uint32_t rt0 = kSplit ? 2u * (wave & 1u) : 0u;                    // first row tile
-  const uint32_t cb0 = kSplit ? wave >> 1 : wave, cbs = kSplit ? 2u : 4u;  // column blocks
 
-  // global offsets of the high tile bits (all of them targets)
-  for (uint32_t h = threadIdx.x; h < (1u << G.n_hi); h += kDenseThreads) {
-    uint32_t off = 0;
-    for (uint32_t j = 0; j < G.n_hi; ++j)
-      if ((h >> j) & 1u) off |= 1u << G.hi_bit[j];
-    hi_tab[h] = off;
-  }
-
-  // U fragments: A[i][kk] = U[16 (rt0 + rt) + i][4 ks + kk]
+  // U fragments: A[i][kk] = U[16 rt + i][4 ks + kk]
   const cptr<cplx<R>> U = to_const(U_);
   R ur[RT][KS], ui[RT][KS];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const uint32_t e = (16u * (rt0 + rt) + li) * K + 4u * ks + lk;
+      const uint32_t e = (16u * rt + li) * K + 4u * ks + lk;
       ur[rt][ks] = U[e].re;
       ui[rt][ks] = U[e].im;
     }
-  // tile positions of the rows this lane reads (B operand) and writes (D)
-  const uint32_t colmask = (M - 1u) & ~G.rowmask;
-  uint32_t brow[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) brow[ks] = deposit(4u * ks + lk, G.rowmask);
-  uint32_t drow[RT][4];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      drow[rt][v] = deposit(16u * (rt0 + rt) + (sizeof(R) == 4 ? 4u * lk + v : lk + 4u * v), G.rowmask);
+  // rows a lane reads, 4 ks + lk, and writes, 16 rt + (4 lk + v or lk + 4 v)
+  const DenseBits B(G);
+  constexpr int kV = sizeof(R) == 4 ? 0 : 2;  // the row bits of register v in D
+  const uint32_t rd = B.col_lane(li) + B.rows(lk, 0, 2), wr = B.col_lane(li) + B.rows(lk, 2 - kV, 2);
   const uint32_t ncb = (1u << G.c) >> 4;
-  __syncthreads();
-
-  // complex64 k = 6 (2^12-amplitude tiles, eight pair accesses per thread):
-  // the first kPre accesses of the next tile are issued before this tile's
-  // contraction (the register file holds no more at three waves per SIMD),
-  // the rest at the top of the tile's turn.  (Measured: prefetching k = 4 and
-  // k = 5 tiles, which are HBM-bound, gains nothing or loses.)
-  constexpr int kAcc = K / 8;
-  constexpr int kPre = kSplit ? 4 : 0;
-  constexpr bool kPipe = kPre > 0;
-  const bool pipe = kPipe && M == 2u * kDenseThreads * kAcc;  // full tiles (n - k >= 6)
-  auto tile_base = [&](uint32_t t) {
-    uint32_t base = 0;
-    for (uint32_t j = 0; j < G.n_free; ++j)
-      if ((t >> j) & 1u) base |= 1u << G.free_bit[j];
-    return base;
-  };
-  cplx2<R> pre[kPipe ? kPre : 1];
-  auto issue_pre = [&](uint32_t base) {
-    if (G.keep) dense_issue<true, R, 0, kPre>(psi, base, G.L, hi_tab, pre);
-    else dense_issue<false, R, 0, kPre>(psi, base, G.L, hi_tab, pre);
-  };
-  if constexpr (kPipe) {
-    if (pipe && blockIdx.x < G.n_tiles) issue_pre(tile_base(blockIdx.x));
-  }
+  // complex128: one 16-byte amplitude per lane and access (in pairs, a wave's
+  // access covers every other 16 bytes of its lines: k = 5 at 27 qubits 1380
+  // against 810 us).  No prefetch of the next tile: at k = 4 and 5 it gains
+  // nothing or loses.
+  constexpr int W = sizeof(R) == 8 ? 1 : 2;
+  const DenseIO<R, W, K * 64 / (W * kDenseThreads), kDenseThreads> io(psi, G);
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
-    // coset bits of tile t (the state bits outside the tile)
-    const uint32_t base = tile_base(t);
-    // load: tile bit 0 is state bit 0, so pairs (p, p + 1) are adjacent
-    if (kPipe && pipe) {
-      if constexpr (kPre < kAcc) {
-        cplx2<R> rest[kAcc > kPre ? kAcc - kPre : 1];
-        if (G.keep) dense_issue<true, R, kPre, kAcc>(psi, base, G.L, hi_tab, rest);
-        else dense_issue<false, R, kPre, kAcc>(psi, base, G.L, hi_tab, rest);
-        dense_put<R, 0, kPre>(T, pre);
-        dense_put<R, kPre, kAcc>(T, rest);
-      } else {
-        dense_put<R, 0, kPre>(T, pre);
-      }
-    } else if constexpr (sizeof(R) == 8 && K == 16) {
-      // complex128, k = 4 (K = 16, memory-bound): one 16-byte amplitude per lane and
-      // access (for k = 5 the extra address work costs more than it saves)
-      if (G.keep) dense_load1<true>(psi, T, M, base, G.L, hi_tab);
-      else dense_load1<false>(psi, T, M, base, G.L, hi_tab);
-    } else {
-      if (G.keep) dense_load<true, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
-      else dense_load<false, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
-    }
+    const uint32_t base = dense_tile_base(t, G);
+    io.load(G.keep, base, T);
     __syncthreads();
-    if constexpr (kPipe) {
-      if (pipe && t + gridDim.x < G.n_tiles)
-        issue_pre(tile_base(t + gridDim.x));
-    }
-
-    // uniform trip count: with split row tiles the two waves of a pair read
-    // all rows of a column block and each writes half of them back in place,
-    // so a barrier separates every round's reads from its writes
-    const uint32_t trips = (ncb + cbs - 1u) / cbs;
-    for (uint32_t it = 0; it < trips; ++it) {
-      const uint32_t cb = cb0 + it * cbs;
-      const bool active = cb < ncb;
-      const uint32_t colp = deposit(16u * (active ? cb : 0u) + li, colmask);
+    for (uint32_t cb = wave; cb < ncb; cb += 4u) {
+      const uint32_t colp = B.col_block(cb);
       acc_t yr[RT], yi[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         yr[rt] = acc_t{0, 0, 0, 0};
         yi[rt] = acc_t{0, 0, 0, 0};
       }
-      if (active) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const cplx<R> x = T[dense_lds_off(brow[ks] | colp)];
-          const R nxi = -x.im;
+      for (int ks = 0; ks < KS; ++ks) {
+        const cplx<R> x = T[rd + colp + B.rows(ks, 2, 3)];
+        const R nxi = -x.im;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          yr[rt] = mfma16(ur[rt][ks], x.re, yr[rt]);
+          yr[rt] = mfma16(ui[rt][ks], nxi, yr[rt]);
+          yi[rt] = mfma16(ur[rt][ks], x.im, yi[rt]);
+          yi[rt] = mfma16(ui[rt][ks], x.re, yi[rt]);
+        }
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          T[wr + colp + B.rows(v, kV, 2) + B.rows(rt, 4, 1)] = cplx<R>{yr[rt][v], yi[rt][v]};
+    }
+    __syncthreads();
+    io.store(base, T);
+    __syncthreads();
+  }
+}
+
+// ---- complex64 k = 5 and 6 on the bf16 matrix cores ----------------------------
+// The FP32 matrix cores make k = 5 and 6 compute-bound (27 qubits: 438 and 679 us
+// against the 380 us that the state's traffic takes).  A float is the exact sum
+// of three bf16 numbers (8 significant bits each, signs absorbing the rest), so
+// U X = sum_ij U_i X_j with every product exact in the FP32 accumulators; the six
+// products with i + j <= 4 are taken, the three left out are below 2^-24 of
+// |u| |x| in all and of random sign.  Six bf16 products cost 6 / 16 of an FP32
+// one, and 32 of them enter an accumulator per instruction instead of 4, so fewer
+// sums are rounded: against complex128, the error of a block (amplitudes of
+// unit size, 9 to 20 qubits) is 0.78e-7 rms and 10.4e-7 at most for k = 5 and
+// 1.30e-7 and 17.2e-7 for k = 6, with the FP32 forms 1.48e-7 and 15.1e-7, and
+// 2.05e-7 and 24.1e-7; after 40 blocks 4.9e-7 and 8.2e-7 rms against 9.2e-7 and
+// 13.0e-7.  k = 5 is then bound by HBM, k = 6 by the
+// bf16 products and the splitting of X (each about 160 us of the 464).
+// V_MFMA_F32_16X16X32_BF16: lane l holds row (A) or column (B) l % 16 and the
+// eight depths of its quarter l / 16 (A and B alike, so the contraction does not
+// depend on their order); D as for the FP32 16x16 forms.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// x = h + m + l, eight numbers at a time (converted in pairs).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct Split8 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ uint32_t to_bf16x2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ void split8(const float (&x)[8], Split8& S) {
+  u32x4 h, m, l;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    h[e] = to_bf16x2(x[2 * e], x[2 * e + 1]);
+    const float r0 = x[2 * e] - __uint_as_float(h[e] << 16);
+    const float r1 = x[2 * e + 1] - __uint_as_float(h[e] & 0xffff0000u);
+    m[e] = to_bf16x2(r0, r1);
+    l[e] = to_bf16x2(r0 - __uint_as_float(m[e] << 16), r1 - __uint_as_float(m[e] & 0xffff0000u));
+  }
+  S.h = __builtin_bit_cast(bf16x8, h);
+  S.m = __builtin_bit_cast(bf16x8, m);
+  S.l = __builtin_bit_cast(bf16x8, l);
+}
+__device__ __forceinline__ f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// c + a b, the small products first.
+__device__ __forceinline__ f32x4 mfma_split(const Split8& a, const Split8& b, f32x4 c) {
+  c = mfma_bf16(a.l, b.h, c);
+  c = mfma_bf16(a.h, b.l, c);
+  c = mfma_bf16(a.m, b.m, c);
+  c = mfma_bf16(a.m, b.h, c);
+  c = mfma_bf16(a.h, b.m, c);
+  return mfma_bf16(a.h, b.h, c);
+}
+
+// The finite floats from here on round to infinity in bf16, and an infinity's
+// remainder is no number: such a block takes the FP32 forms.
+constexpr float kSplitMax = 0x1.ffp127f;
+// max(m, |a|, |b|) in one instruction (fmaxf first canonicalises each operand)
+__device__ __forceinline__ float max3_abs(float m, float a, float b) {
+  asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
+  return m;
+}
+
+// k = 6: the two waves of a pair take the same column blocks, each two of U's
+// four 16-row tiles, with a barrier between a block's reads and its in-place
+// writes; k = 5: a wave takes whole column blocks.  At k = 6 the next tile's
+// loads are issued before this tile's contraction (two waves per SIMD hold them
+// and U's split fragments; three spill).
+template <int K>
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(K == 64 ? 2 : 3)))
+dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGeom G) {
+  constexpr int kSlabs = K / 32, RT = 2;
+  constexpr bool kPair = K == 64;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cplx<float>* T = reinterpret_cast<cplx<float>*>(smem_raw);
+  uint32_t* unfit = reinterpret_cast<uint32_t*>(smem_raw + sizeof(cplx<float>) * dense_lds_off(1u << G.m));
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t li = lane & 15u, lk = lane >> 4;
+  const uint32_t rt0 = kPair ? 2u * (wave & 1u) : 0u;
+  const uint32_t cb0 = kPair ? wave >> 1 : wave, cbs = kPair ? 2u : 4u;
+  if (threadIdx.x == 0) *unfit = 0u;
+  const DenseIO<float, 2, K / 8, kDenseThreads> io(psi, G);
+  cplx2<float> pre[K / 8];
+  if (kPair && blockIdx.x < G.n_tiles) io.issue(G.keep, dense_tile_base(blockIdx.x, G), pre);
+  Split8 ur[RT][kSlabs], ui[RT][kSlabs];
+  float xmax = 0.0f;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int sl = 0; sl < kSlabs; ++sl) {
+      const cplx<float>* u = U_ + (16u * (rt0 + rt) + li) * K + 32u * sl + 8u * lk;
+      float re[8], im[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        re[e] = u[e].re;
+        im[e] = u[e].im;
+        xmax = max3_abs(xmax, re[e], im[e]);
+      }
+      split8(re, ur[rt][sl]);
+      split8(im, ui[rt][sl]);
+    }
+  // rows a lane reads, 32 sl + 8 lk + e, and writes, 16 (rt0 + rt) + 4 lk + v
+  const DenseBits B(G);
+  const uint32_t rd = B.col_lane(li) + B.rows(lk, 3, 2);
+  const uint32_t wr = B.col_lane(li) + B.rows(lk, 2, 2) + (rt0 ? B.row[5] : 0u);
+  const uint32_t ncb = (1u << G.c) >> 4;
+  const uint32_t trips = (ncb + cbs - 1u) / cbs;  // uniform: barriers inside
+  for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
+    const uint32_t base = dense_tile_base(t, G);
+    if constexpr (kPair) {
+      io.put(T, pre);
+      if (t + gridDim.x < G.n_tiles) io.issue(G.keep, dense_tile_base(t + gridDim.x, G), pre);
+    } else {
+      io.load(G.keep, base, T);
+    }
+    __syncthreads();
+    for (uint32_t it = 0; it < trips; ++it) {
+      const uint32_t cb = cb0 + it * cbs;
+      const bool on = cb < ncb;
+      const uint32_t colp = B.col_block(cb);
+      f32x4 rr[RT], ii[RT], ri[RT];  // Ur Xr, Ui Xi, Ur Xi + Ui Xr
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) rr[rt] = ii[rt] = ri[rt] = f32x4{0, 0, 0, 0};
+      if (on) {
+#pragma unroll
+        for (int sl = 0; sl < kSlabs; ++sl) {
+          float re[8], im[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const cplx<float> x = T[rd + colp + B.rows(e, 0, 3) + (sl ? B.row[5] : 0u)];
+            re[e] = x.re;
+            im[e] = x.im;
+            xmax = max3_abs(xmax, x.re, x.im);
+          }
+          Split8 xr, xi;
+          split8(re, xr);
+          split8(im, xi);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
-            yr[rt] = mfma16(ur[rt][ks], x.re, yr[rt]);
-            yr[rt] = mfma16(ui[rt][ks], nxi, yr[rt]);
-            yi[rt] = mfma16(ur[rt][ks], x.im, yi[rt]);
-            yi[rt] = mfma16(ui[rt][ks], x.re, yi[rt]);
+            rr[rt] = mfma_split(ur[rt][sl], xr, rr[rt]);
+            ii[rt] = mfma_split(ui[rt][sl], xi, ii[rt]);
+            ri[rt] = mfma_split(ur[rt][sl], xi, ri[rt]);
+            ri[rt] = mfma_split(ui[rt][sl], xr, ri[rt]);
           }
         }
       }
-      if constexpr (kSplit) __syncthreads();
-      if (active) {
+      if constexpr (kPair) __syncthreads();
+      if (on) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) T[dense_lds_off(drow[rt][v] | colp)] = cplx<R>{yr[rt][v], yi[rt][v]};
+          for (int v = 0; v < 4; ++v)
+            T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] = cplx<float>{rr[rt][v] - ii[rt][v], ri[rt][v]};
       }
     }
+    if (__any(xmax >= kSplitMax) && lane == 0) *unfit = 1u;  // and so for the tiles that follow
     __syncthreads();
-    if constexpr (sizeof(R) == 8 && K == 16) {
-      if (G.keep) dense_store1<true>(psi, T, M, base, G.L, hi_tab);
-      else dense_store1<false>(psi, T, M, base, G.L, hi_tab);
-    } else {
-      if (G.keep) dense_store<true, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
-      else dense_store<false, R, dense_io<R, K>()>(psi, T, M, base, G.L, hi_tab);
+    if (__builtin_expect(*unfit, 0u)) {
+      io.load(false, base, T);  // the state still holds the tile
+      __syncthreads();
+      for (uint32_t it = 0; it < trips; ++it) {
+        const uint32_t cb = cb0 + it * cbs;
+        const uint32_t colp = cb < ncb ? B.col_block(cb) : 0u;
+        f32x4 yr[RT], yi[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) yr[rt] = yi[rt] = f32x4{0, 0, 0, 0};
+#pragma unroll 1
+        for (uint32_t ks = 0; ks < (uint32_t)K / 4u; ++ks) {
+          const cplx<float> x = T[B.col_lane(li) + colp + B.rows(lk, 0, 2) + B.rows(ks, 2, 4)];
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            const cplx<float> u = U_[(16u * (rt0 + rt) + li) * K + 4u * ks + lk];
+            yr[rt] = mfma16(u.re, x.re, yr[rt]);
+            yr[rt] = mfma16(u.im, -x.im, yr[rt]);
+            yi[rt] = mfma16(u.re, x.im, yi[rt]);
+            yi[rt] = mfma16(u.im, x.re, yi[rt]);
+          }
+        }
+        if constexpr (kPair) __syncthreads();
+        if (cb < ncb) {
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] = cplx<float>{yr[rt][v], yi[rt][v]};
+        }
+      }
+      __syncthreads();
     }
+    io.store(base, T);
     __syncthreads();
   }
 }
@@ -348,63 +462,33 @@ __global__ void __launch_bounds__(kThreads6) dense_kernel_k6_c128(cplx<double>* 
   constexpr uint32_t NT = kThreads6;
   typedef f64x4 acc_t;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const uint32_t M = 1u << G.m;
   cplx<double>* T = reinterpret_cast<cplx<double>*>(smem_raw);
-  cplx<double>* Us = T + dense_lds_off(M);
-  uint32_t* hi_tab = reinterpret_cast<uint32_t*>(Us + K * kUsStride);
-  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  cplx<double>* Us = T + dense_lds_off(1u << G.m);
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t li = lane & 15u, lk = lane >> 4;
   const uint32_t rt0 = 2u * (wave & 1u), cb0 = wave >> 1, cbs = NT / 128u;
-  for (uint32_t h = threadIdx.x; h < (1u << G.n_hi); h += NT) {
-    uint32_t off = 0;
-    for (uint32_t j = 0; j < G.n_hi; ++j)
-      if ((h >> j) & 1u) off |= 1u << G.hi_bit[j];
-    hi_tab[h] = off;
-  }
+  // the next tile's loads are issued before this tile's contraction (one
+  // workgroup per CU: tile and matrix fill the LDS); one amplitude per lane and
+  // access (1236 us at 27 qubits, in pairs 1350)
+  const DenseIO<double, 1, 8, NT> io(psi, G);
+  cplx<double> pre[8];
+  if (blockIdx.x < G.n_tiles) io.issue(G.keep, dense_tile_base(blockIdx.x, G), pre);
   for (uint32_t e = threadIdx.x; e < (uint32_t)(K * K); e += NT) Us[(e / K) * kUsStride + e % K] = U_[e];
-  const uint32_t colmask = (M - 1u) & ~G.rowmask;
-  uint32_t brow[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) brow[ks] = deposit(4u * ks + lk, G.rowmask);
-  uint32_t drow[RT][4];
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) drow[rt][v] = deposit(16u * (rt0 + rt) + lk + 4u * v, G.rowmask);
+  const DenseBits B(G);
+  const uint32_t rd = B.col_lane(li) + B.rows(lk, 0, 2);
+  const uint32_t wr = rd + (rt0 ? B.row[5] : 0u);
   const uint32_t ncb = (1u << G.c) >> 4;
   const uint32_t trips = (ncb + cbs - 1u) / cbs;
-  __syncthreads();
-
-  // the next tile's loads are issued before this tile's contraction (one
-  // workgroup per CU: tile and matrix fill the LDS)
-  constexpr int kAcc = 4;
-  const bool pipe = M == 2u * NT * kAcc;  // full tiles (n - k >= 6)
-  auto tile_base = [&](uint32_t t) {
-    uint32_t base = 0;
-    for (uint32_t j = 0; j < G.n_free; ++j)
-      if ((t >> j) & 1u) base |= 1u << G.free_bit[j];
-    return base;
-  };
-  cplx2<double> pre[kAcc];
-  auto issue_pre = [&](uint32_t base) {
-    if (G.keep) dense_issue<true, double, 0, kAcc, NT>(psi, base, G.L, hi_tab, pre);
-    else dense_issue<false, double, 0, kAcc, NT>(psi, base, G.L, hi_tab, pre);
-  };
-  if (pipe && blockIdx.x < G.n_tiles) issue_pre(tile_base(blockIdx.x));
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
-    const uint32_t base = tile_base(t);
-    if (pipe)
-      dense_put<double, 0, kAcc, NT>(T, pre);
-    else
-      if (G.keep) dense_load<true, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
-      else dense_load<false, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+    const uint32_t base = dense_tile_base(t, G);
+    io.put(T, pre);
     __syncthreads();
-    if (pipe && t + gridDim.x < G.n_tiles)
-      issue_pre(tile_base(t + gridDim.x));
+    if (t + gridDim.x < G.n_tiles) io.issue(G.keep, dense_tile_base(t + gridDim.x, G), pre);
     for (uint32_t it = 0; it < trips; ++it) {
       const uint32_t cb = cb0 + it * cbs;
       const bool active = cb < ncb;
-      const uint32_t colp = deposit(16u * (active ? cb : 0u) + li, colmask);
+      const uint32_t colp = B.col_block(cb);
       acc_t yr[RT], yi[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -414,7 +498,7 @@ __global__ void __launch_bounds__(kThreads6) dense_kernel_k6_c128(cplx<double>* 
       if (active) {
 #pragma unroll 4
         for (int ks = 0; ks < KS; ++ks) {
-          const cplx<double> x = T[dense_lds_off(brow[ks] | colp)];
+          const cplx<double> x = T[rd + colp + B.rows(ks, 2, 4)];
           const double nxi = -x.im;
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
@@ -431,12 +515,12 @@ __global__ void __launch_bounds__(kThreads6) dense_kernel_k6_c128(cplx<double>* 
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) T[dense_lds_off(drow[rt][v] | colp)] = cplx<double>{yr[rt][v], yi[rt][v]};
+          for (int v = 0; v < 4; ++v)
+            T[wr + colp + B.rows(v, 2, 2) + B.rows(rt, 4, 1)] = cplx<double>{yr[rt][v], yi[rt][v]};
       }
     }
     __syncthreads();
-    if (G.keep) dense_store<true, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
-    else dense_store<false, double, 2, NT>(psi, T, M, base, G.L, hi_tab);
+    io.store(base, T);
     __syncthreads();
   }
 }
@@ -474,9 +558,7 @@ DenseGeom dense_geometry(int n, int k, const int* bits_sorted) {
       ++pos;
     }
   G.rowmask = rowmask;
-  for (int b = 0; b < n; ++b)
-    if (!((bmask >> b) & 1u)) G.free_bit[G.n_free++] = (uint32_t)b;
-  G.n_tiles = 1u << G.n_free;
+  G.n_tiles = 1u << (n - k - c);
   return G;
 }
 
@@ -488,17 +570,32 @@ bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx
   // 71 us; cached writes 81, the tiles' short runs evicting each other)
   G.keep = keep_resident(sizeof(cplx<R>) << n);
   const uint32_t M = 1u << G.m;
-  const size_t lds = sizeof(cplx<R>) * (M + ((M >> 5) << 1)) + 64 * sizeof(uint32_t);
-  const uint32_t grid = G.n_tiles < 2048u ? G.n_tiles : 2048u;
+  const size_t lds = sizeof(cplx<R>) * (M + ((M >> 5) << 1)) + sizeof(uint32_t);
+  // Two workgroups per CU.  With more, those in flight walk the state further
+  // apart and U is read and split more often (27 qubits complex64, k = 5: 355 us,
+  // with 1024 441, with 2048 398, with one per tile 476; complex128 k = 4 756,
+  // 2048 825); with one, loads are too few (518).  Exceptions, measured the same
+  // way: complex64 k = 4 (8 KB tiles) three (370 us, two 411); complex128 k = 6 one,
+  // what the LDS holds (21 qubits 27 us, two 32); complex64 k = 6 more once a
+  // workgroup would take over 16 tiles (28 qubits: 828 us, two 926; 25 qubits: two 115,
+  // eight 126).
+  uint32_t wgs = 512u;
+  if (sizeof(R) == 4 && k == 4) wgs = 768u;
+  if (sizeof(R) == 4 && k == 6 && G.n_tiles / 16u > wgs) wgs = G.n_tiles / 16u;
+  if (sizeof(R) == 8 && k == 6) wgs = 256u;
+  const uint32_t grid = G.n_tiles < wgs ? G.n_tiles : wgs;
   if (k == 4) {
     QS_LAUNCH("dense_k4", s, (dense_kernel<R, 16>), dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
   } else if (k == 5) {
-    QS_LAUNCH("dense_k5", s, (dense_kernel<R, 32>), dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
+    if constexpr (sizeof(R) == 4)
+      QS_LAUNCH("dense_k5", s, dense_split_kernel<32>, dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
+    else
+      QS_LAUNCH("dense_k5", s, (dense_kernel<R, 32>), dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
   } else if constexpr (sizeof(R) == 4) {
-    QS_LAUNCH("dense_k6", s, (dense_kernel<R, 64>), dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
+    QS_LAUNCH("dense_k6", s, dense_split_kernel<64>, dim3(grid), dim3(kDenseThreads), lds, s, psi, U_dev, G);
   } else {
-    // the tile, the 64 x 64 complex128 matrix (rows padded) and the offset table: ~136 KB
-    const size_t lds6 = lds + sizeof(cplx<double>) * 64 * kUsStride;
+    // the tile, the 64 x 64 complex128 matrix (rows padded): ~134 KB
+    const size_t lds6 = sizeof(cplx<double>) * (M + ((M >> 5) << 1)) + sizeof(cplx<double>) * 64 * kUsStride;
     static bool attr_set = false;
     if (!attr_set) {
       allow_dynamic_lds((const void*)dense_kernel_k6_c128, (int)lds6, "dense_k6");

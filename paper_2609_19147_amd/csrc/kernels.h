@@ -152,10 +152,8 @@ struct DenseGeom {
   uint32_t m, c, L;        // tile bits, column bits, low tile bits equal to state bits [0, L)
   uint32_t rowmask;        // tile positions of the targets
   uint32_t n_hi;           // tile bits at positions >= L (all targets) ...
-  uint32_t hi_bit[6];      // ... and their state bits
-  uint32_t n_free;         // state bits outside the tile (ascending) ...
-  uint32_t free_bit[32];
-  uint32_t n_tiles;        // 2^n_free
+  uint32_t hi_bit[6];      // ... and their state bits (ascending)
+  uint32_t n_tiles;        // 2^(state bits outside the tile)
   uint32_t keep;           // 1: cached accesses to psi (keep_resident)
 };
 bool dense_supported(int n, int k, bool complex128);
