@@ -229,6 +229,44 @@ __device__ __forceinline__ void pipe_to_lds(const typename PipeAccess<R>::T* v, 
   }
 }
 
+// tile_store for a tile of exactly kN accesses per thread: with the number of
+// stores known, the wait for the next coset's loads, issued before them, does not
+// wait for them too (a loop of stores does: it counts as any number).
+template <class R, int kN>
+__device__ __forceinline__ double pipe_store(const TileKArgs<R>& A, const Ctx& C, const cplx<R>* T) {
+  using E = typename PipeAccess<R>::T;
+  constexpr uint32_t apa = PipeAccess<R>::amps;
+  constexpr int kB = kN < kChunk * 2 / (int)apa ? kN : kChunk * 2 / (int)apa;
+  const uint32_t step = apa * blockDim.x, p0 = apa * threadIdx.x;
+  const R sc = (R)A.scale;
+  const bool do_scale = A.scale != 1.0;
+  double nacc = 0.0;
+#pragma unroll
+  for (int b = 0; b < kN; b += kB) {
+    union {
+      E e;
+      cplx<R> c[apa];
+    } v[kB];
+#pragma unroll
+    for (int k = 0; k < kB; ++k) v[k].e = *reinterpret_cast<const E*>(T + lds_off(p0 + step * (b + k)));
+    if (do_scale) {
+#pragma unroll
+      for (int k = 0; k < kB; ++k)
+#pragma unroll
+        for (int i = 0; i < (int)apa; ++i) v[k].c[i] = cscale(v[k].c[i], sc);
+    }
+#pragma unroll
+    for (int k = 0; k < kB; ++k) st_nt(reinterpret_cast<E*>(A.psi + (C.base | C.dep(p0 + step * (b + k)))), v[k].e);
+    if (A.norm_part != nullptr) {
+#pragma unroll
+      for (int k = 0; k < kB; ++k)
+#pragma unroll
+        for (int i = 0; i < (int)apa; ++i) nacc += abs2_d(v[k].c[i]);
+    }
+  }
+  return nacc;
+}
+
 // Requires 2^m = blockDim.x * kPipeK * PipeAccess<R>::amps (checked on the host).
 template <class R>
 __global__ void __launch_bounds__(kMaxThreads) tile_kernel_pipe(TileKArgs<R> A, uint32_t n_cosets) {
@@ -253,7 +291,7 @@ __global__ void __launch_bounds__(kMaxThreads) tile_kernel_pipe(TileKArgs<R> A, 
     __syncthreads();
     if (c + G < n_cosets) pipe_issue<R, 0, P>(A, coset_ctx(A, c + G), v);
     tile_rounds<R, false>(A, C, T, blockDim.x, threadIdx.x);
-    const double nacc = tile_store<R>(A, C, T, blockDim.x);
+    const double nacc = pipe_store<R, kPipeK>(A, C, T);
     if (A.norm_part != nullptr) {
       const double t = block_sum_fixed(nacc);
       if (threadIdx.x == 0) A.norm_part[c] = t;
@@ -410,8 +448,8 @@ tile_kernel_dual_pipe(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q, double* __res
       tile_rounds<R, false, true>(A, C, T0, blockDim.x, threadIdx.x, T1);
     }
     if (Q.nbits) rho::accumulate_tile<R>(T0, T1, M, Q, red, partials, c, n_cosets);
-    tile_store<R>(A, C, T0, blockDim.x);
-    tile_store<R>(B, C, T1, blockDim.x);
+    pipe_store<R, kDualPipeK>(A, C, T0);
+    pipe_store<R, kDualPipeK>(B, C, T1);
   }
 }
 
