@@ -168,13 +168,15 @@ void record(qs_batch& B) {
       const LayerIR& L0 = P0.layers[li];
       if (L0.kind == L_TILE) {
         const TilePassIR& T = P0.passes[L0.index];
-        bool has_diag = false;
+        bool has_diag = false, has_qft = false;
         for (size_t i : G.inst) {
           const qs_plan& p = *B.plans[i];
-          has_diag = has_diag || !p.ir.passes[p.ir.layers[li].index].diag_slots.empty();
+          const TilePassIR& pass = p.ir.passes[p.ir.layers[li].index];
+          has_diag = has_diag || !pass.diag_slots.empty();
+          has_qft = has_qft || pass_has_qft(pass);
         }
         launch_tile_batched<R>((const TileKArgs<R>*)((char*)B.desc + B.slot_desc[gi][li]), (uint32_t)G.inst.size(),
-                               (uint32_t)G.n, (uint32_t)(T.L + T.h), has_diag, B.stream);
+                               (uint32_t)G.n, (uint32_t)(T.L + T.h), has_diag, has_qft, B.stream);
       } else {
         // other layer kinds: one launch per instance
         for (size_t i : G.inst) apply_layers(*B.views[i], *B.plans[i], li, li + 1);

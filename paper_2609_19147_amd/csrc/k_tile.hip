@@ -149,14 +149,14 @@ __device__ __forceinline__ double tile_store(const TileKArgs<R>& A, const Ctx& C
 }
 // kKeep: cached accesses to the state.  A template parameter: a branch in one
 // kernel cost the streaming passes 1 to 3% (a larger kernel, more scalar spills).
-template <class R, bool kDiag, bool kKeep = false>
+template <class R, bool kDiag, bool kKeep = false, int kQft = 2>
 __device__ __forceinline__ void tile_body(const TileKArgs<R>& A, const uint32_t coset) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<R>* T = reinterpret_cast<cplx<R>*>(smem_raw);
   const Ctx C = coset_ctx(A, coset);
   tile_load<R, kKeep>(A, C, T);
   __syncthreads();
-  tile_rounds<R, kDiag>(A, C, T, blockDim.x, threadIdx.x);
+  tile_rounds<R, kDiag, false, kQft>(A, C, T, blockDim.x, threadIdx.x);
   const double nacc = tile_store<R, kKeep>(A, C, T, blockDim.x);
   if (A.norm_part != nullptr) {
     const double t = block_sum_fixed(nacc);
@@ -164,18 +164,18 @@ __device__ __forceinline__ void tile_body(const TileKArgs<R>& A, const uint32_t 
   }
 }
 
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) tile_kernel(TileKArgs<R> A) {
-  tile_body<R, kDiag>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
+  tile_body<R, kDiag, false, kQft>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
 }
 
 // complex64 passes: registers capped at 128 so that four waves fit per SIMD
 // (two 512-thread workgroups of 2^13-amplitude tiles, or four of 2^12, share
 // a CU's LDS).
-template <bool kDiag, bool kKeep>
+template <bool kDiag, bool kKeep, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(4)))
 tile_kernel_c64(TileKArgs<float> A) {
-  tile_body<float, kDiag, kKeep>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
+  tile_body<float, kDiag, kKeep, kQft>(A, A.order ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x));
 }
 
 // ---- software-pipelined tile passes ------------------------------------------
@@ -268,7 +268,7 @@ __device__ __forceinline__ double pipe_store(const TileKArgs<R>& A, const Ctx& C
 }
 
 // Requires 2^m = blockDim.x * kPipeK * PipeAccess<R>::amps (checked on the host).
-template <class R>
+template <class R, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) tile_kernel_pipe(TileKArgs<R> A, uint32_t n_cosets) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<R>* T = reinterpret_cast<cplx<R>*>(smem_raw);
@@ -290,7 +290,7 @@ __global__ void __launch_bounds__(kMaxThreads) tile_kernel_pipe(TileKArgs<R> A, 
     }
     __syncthreads();
     if (c + G < n_cosets) pipe_issue<R, 0, P>(A, coset_ctx(A, c + G), v);
-    tile_rounds<R, false>(A, C, T, blockDim.x, threadIdx.x);
+    tile_rounds<R, false, false, kQft>(A, C, T, blockDim.x, threadIdx.x);
     const double nacc = pipe_store<R, kPipeK>(A, C, T);
     if (A.norm_part != nullptr) {
       const double t = block_sum_fixed(nacc);
@@ -334,7 +334,7 @@ __device__ __forceinline__ void ws_to_lds(const typename PipeAccess<R>::T* v, ui
 
 // Requires 2^m = kWsProducers * kWsK * PipeAccess<R>::amps and norm_part == null
 // (checked on the host).
-template <class R>
+template <class R, int kQft>
 __global__ void __launch_bounds__(kWsConsumers + kWsProducers) tile_kernel_ws(TileKArgs<R> A, uint32_t n_cosets) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<R>* T = reinterpret_cast<cplx<R>*>(smem_raw);
@@ -363,7 +363,7 @@ __global__ void __launch_bounds__(kWsConsumers + kWsProducers) tile_kernel_ws(Ti
     for (uint32_t c = c0; c < n_cosets; c += G) {
       const bool next = c + G < n_cosets;
       const Ctx C = coset_ctx(A, c);
-      tile_rounds<R, false>(A, C, T, kWsConsumers, threadIdx.x);
+      tile_rounds<R, false, false, kQft>(A, C, T, kWsConsumers, threadIdx.x);
       tile_store<R>(A, C, T, kWsConsumers);
       __syncthreads();  // tile read out of LDS
       if (next) __syncthreads();  // next tile in LDS
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(kWsConsumers + kWsProducers) tile_kernel_ws(Ti
 // the cross densities of the layer's parameter bits are summed from the two
 // resulting tiles, and both tiles are stored back -- 4 S of HBM traffic per
 // layer instead of 6 S for two passes and a separate re-read of both states.
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 2 : 1)))
 tile_kernel_dual(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q,
                                                                  double* __restrict__ partials) {
@@ -394,8 +394,8 @@ tile_kernel_dual(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q,
   tile_load<R>(A, C, T0);
   tile_load<R>(B, C, T1);
   __syncthreads();
-  tile_rounds<R, kDiag>(A, C, T0, blockDim.x, threadIdx.x);
-  tile_rounds<R, kDiag>(A, C, T1, blockDim.x, threadIdx.x);
+  tile_rounds<R, kDiag, false, kQft>(A, C, T0, blockDim.x, threadIdx.x);
+  tile_rounds<R, kDiag, false, kQft>(A, C, T1, blockDim.x, threadIdx.x);
   if (Q.nbits) rho::accumulate_tile<R>(T0, T1, M, Q, red, partials, coset, ntiles);
   tile_store<R>(A, C, T0, blockDim.x);
   tile_store<R>(B, C, T1, blockDim.x);
@@ -410,7 +410,7 @@ tile_kernel_dual(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q,
 // 2^m = blockDim.x * kDualPipeK * 2 (eight 16-byte accesses per thread and
 // tile; checked on the host).
 constexpr int kDualPipeK = 8;
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(2)))
 tile_kernel_dual_pipe(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q, double* __restrict__ partials,
                       uint32_t n_cosets) {
@@ -442,10 +442,10 @@ tile_kernel_dual_pipe(TileKArgs<R> A, cplx<R>* lam, RhoTileArgs Q, double* __res
       pipe_issue<R, 0, kDualPipeK>(B, Cn, v1);
     }
     if constexpr (kDiag) {
-      tile_rounds<R, kDiag>(A, C, T0, blockDim.x, threadIdx.x);
-      tile_rounds<R, kDiag>(A, C, T1, blockDim.x, threadIdx.x);
+      tile_rounds<R, kDiag, false, kQft>(A, C, T0, blockDim.x, threadIdx.x);
+      tile_rounds<R, kDiag, false, kQft>(A, C, T1, blockDim.x, threadIdx.x);
     } else {
-      tile_rounds<R, false, true>(A, C, T0, blockDim.x, threadIdx.x, T1);
+      tile_rounds<R, false, true, kQft>(A, C, T0, blockDim.x, threadIdx.x, T1);
     }
     if (Q.nbits) rho::accumulate_tile<R>(T0, T1, M, Q, red, partials, c, n_cosets);
     pipe_store<R, kDualPipeK>(A, C, T0);
@@ -480,12 +480,12 @@ __device__ __forceinline__ TileKArgs<R> load_args(const TileKArgs<R>* descs, uin
 // Many instances of one tile geometry in one grid: virtual block v (the
 // XCD-aware order of the workgroups) runs coset (v & (2^shift - 1)) of
 // instance (v >> shift).
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 __global__ void __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 1)))
 tile_kernel_batched(const TileKArgs<R>* __restrict__ descs,
                                                                     uint32_t shift) {
   const uint32_t v = xcd_block(blockIdx.x, gridDim.x);
-  tile_body<R, kDiag>(load_args(descs, v >> shift), v & ((1u << shift) - 1u));
+  tile_body<R, kDiag, false, kQft>(load_args(descs, v >> shift), v & ((1u << shift) - 1u));
 }
 
 inline uint32_t tile_threads(uint32_t m) {
@@ -510,49 +510,68 @@ inline size_t tile_lds(uint32_t m, size_t elem) {
 
 }  // namespace
 
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 void launch_tile_batched_k(const TileKArgs<R>* descs_dev, uint32_t count, uint32_t n, uint32_t m, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    allow_dynamic_lds((const void*)tile_kernel_batched<R, kDiag>, kTileDynLds, "tile_pass_batched");
+    allow_dynamic_lds((const void*)tile_kernel_batched<R, kDiag, kQft>, kTileDynLds, "tile_pass_batched");
     attr_set = true;
   }
   const uint32_t shift = n - m;
-  QS_LAUNCH("tile_pass_batched", s, (tile_kernel_batched<R, kDiag>), dim3(count << shift), dim3(tile_threads_for<R, kDiag>(m)),
+  QS_LAUNCH("tile_pass_batched", s, (tile_kernel_batched<R, kDiag, kQft>), dim3(count << shift), dim3(tile_threads_for<R, kDiag>(m)),
             tile_lds(m, sizeof(cplx<R>)), s, descs_dev, shift);
 }
 
 template <class R>
 void launch_tile_batched(const TileKArgs<R>* descs_dev, uint32_t count, uint32_t n, uint32_t m, bool has_diag,
-                         hipStream_t s) {
+                         bool has_qft, hipStream_t s) {
   if (has_diag)
-    launch_tile_batched_k<R, true>(descs_dev, count, n, m, s);
+    has_qft ? launch_tile_batched_k<R, true, 2>(descs_dev, count, n, m, s)
+            : launch_tile_batched_k<R, true, 0>(descs_dev, count, n, m, s);
   else
-    launch_tile_batched_k<R, false>(descs_dev, count, n, m, s);
+    has_qft ? launch_tile_batched_k<R, false, 2>(descs_dev, count, n, m, s)
+            : launch_tile_batched_k<R, false, 0>(descs_dev, count, n, m, s);
 }
 
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 void launch_tile_k(const TileKArgs<R>& A, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    allow_dynamic_lds((const void*)tile_kernel<R, kDiag>, kTileDynLds, "tile_pass");
+    allow_dynamic_lds((const void*)tile_kernel<R, kDiag, kQft>, kTileDynLds, "tile_pass");
     attr_set = true;
   }
   // one thread per register group of a round, between 64 and 512 threads
   const uint32_t n_cosets = 1u << (A.n - A.m);
-  QS_LAUNCH("tile_pass", s, (tile_kernel<R, kDiag>), dim3(n_cosets), dim3(tile_threads_for<R, kDiag>(A.m)),
+  QS_LAUNCH("tile_pass", s, (tile_kernel<R, kDiag, kQft>), dim3(n_cosets), dim3(tile_threads_for<R, kDiag>(A.m)),
             tile_lds(A.m, sizeof(cplx<R>)), s, A);
 }
 
-template <bool kDiag, bool kKeep>
+template <bool kDiag, bool kKeep, int kQft>
 void launch_tile_c64(const TileKArgs<float>& A, hipStream_t s) {
   static bool attr_set = false;
   if (!attr_set) {
-    allow_dynamic_lds((const void*)tile_kernel_c64<kDiag, kKeep>, kTileDynLds, "tile_pass");
+    allow_dynamic_lds((const void*)tile_kernel_c64<kDiag, kKeep, kQft>, kTileDynLds, "tile_pass");
     attr_set = true;
   }
-  QS_LAUNCH("tile_pass", s, (tile_kernel_c64<kDiag, kKeep>), dim3(1u << (A.n - A.m)), dim3(tile_threads(A.m)),
+  QS_LAUNCH("tile_pass", s, (tile_kernel_c64<kDiag, kKeep, kQft>), dim3(1u << (A.n - A.m)), dim3(tile_threads(A.m)),
             tile_lds(A.m, sizeof(cplx<float>)), s, A);
+}
+
+// What a pass has of QFT stages picks its kernel: without their code a kernel is
+// half the size with fewer scalar spills (heisenberg chain on 23 qubits, complex64:
+// 2306 -> 2256 us, TFIM on 25 7835 -> 7763), and a loop over ops next to the
+// straight-line rounds costs those 0.5 to 1% (30-qubit QFT and Walsh passes), in
+// place of the rounds of one stage up to 4% (23-qubit complex128 QFT).
+template <class R, int kQft>
+void launch_tile_q(const TileKArgs<R>& A, hipStream_t s) {
+  A.diag != nullptr ? launch_tile_k<R, true, kQft>(A, s) : launch_tile_k<R, false, kQft>(A, s);
+}
+template <int kQft>
+void launch_tile_c64_q(const TileKArgs<float>& A, hipStream_t s) {
+  if (A.diag != nullptr)
+    A.keep ? launch_tile_c64<true, true, kQft>(A, s) : launch_tile_c64<true, false, kQft>(A, s);
+  else
+    A.keep ? launch_tile_c64<false, true, kQft>(A, s) : launch_tile_c64<false, false, kQft>(A, s);
 }
 
 // Workgroups of a pipelined pass: one per compute unit (at most one coset each).
@@ -583,44 +602,48 @@ bool ws_eligible(const TileKArgs<R>& A) {
          (1u << A.m) == kWsProducers * kWsK * PipeAccess<R>::amps;
 }
 
+template <class R, int kQft>
+void launch_tile_ws(const TileKArgs<R>& A, hipStream_t s) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    allow_dynamic_lds((const void*)tile_kernel_ws<R, kQft>, kTileDynLds, "tile_pass");
+    attr_set = true;
+  }
+  const uint32_t n_cosets = 1u << (A.n - A.m);
+  QS_LAUNCH("tile_pass", s, (tile_kernel_ws<R, kQft>), dim3(pipe_grid(n_cosets)), dim3(kWsConsumers + kWsProducers),
+            tile_lds(A.m, sizeof(cplx<R>)), s, A, n_cosets);
+}
+
+template <class R, int kQft>
+void launch_tile_pipe(const TileKArgs<R>& A, hipStream_t s) {
+  static bool attr_set = false;
+  if (!attr_set) {
+    allow_dynamic_lds((const void*)tile_kernel_pipe<R, kQft>, kTileDynLds, "tile_pass");
+    attr_set = true;
+  }
+  const uint32_t n_cosets = 1u << (A.n - A.m);
+  QS_LAUNCH("tile_pass", s, (tile_kernel_pipe<R, kQft>), dim3(pipe_grid(n_cosets)), dim3(tile_threads(A.m)),
+            tile_lds(A.m, sizeof(cplx<R>)), s, A, n_cosets);
+}
+
 template <class R>
 void launch_tile(const TileKArgs<R>& A, hipStream_t s) {
   if (ws_eligible(A)) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      allow_dynamic_lds((const void*)tile_kernel_ws<R>, kTileDynLds, "tile_pass");
-      attr_set = true;
-    }
-    const uint32_t n_cosets = 1u << (A.n - A.m);
-    QS_LAUNCH("tile_pass", s, tile_kernel_ws<R>, dim3(pipe_grid(n_cosets)), dim3(kWsConsumers + kWsProducers),
-              tile_lds(A.m, sizeof(cplx<R>)), s, A, n_cosets);
+    A.qft == 2 ? launch_tile_ws<R, 2>(A, s) : launch_tile_ws<R, 1>(A, s);
     return;
   }
   if (pipe_eligible(A)) {
-    static bool attr_set = false;
-    if (!attr_set) {
-      allow_dynamic_lds((const void*)tile_kernel_pipe<R>, kTileDynLds, "tile_pass");
-      attr_set = true;
-    }
-    const uint32_t n_cosets = 1u << (A.n - A.m);
-    QS_LAUNCH("tile_pass", s, tile_kernel_pipe<R>, dim3(pipe_grid(n_cosets)), dim3(tile_threads(A.m)),
-              tile_lds(A.m, sizeof(cplx<R>)), s, A, n_cosets);
+    A.qft == 2 ? launch_tile_pipe<R, 2>(A, s) : launch_tile_pipe<R, 1>(A, s);
     return;
   }
   if constexpr (sizeof(R) == 4) {
-    if (A.diag != nullptr)
-      A.keep ? launch_tile_c64<true, true>(A, s) : launch_tile_c64<true, false>(A, s);
-    else
-      A.keep ? launch_tile_c64<false, true>(A, s) : launch_tile_c64<false, false>(A, s);
+    A.qft == 0 ? launch_tile_c64_q<0>(A, s) : (A.qft == 1 ? launch_tile_c64_q<1>(A, s) : launch_tile_c64_q<2>(A, s));
   } else {
-    if (A.diag != nullptr)
-      launch_tile_k<R, true>(A, s);
-    else
-      launch_tile_k<R, false>(A, s);
+    A.qft == 0 ? launch_tile_q<R, 0>(A, s) : (A.qft == 1 ? launch_tile_q<R, 1>(A, s) : launch_tile_q<R, 2>(A, s));
   }
 }
 
-template <class R, bool kDiag>
+template <class R, bool kDiag, int kQft>
 void launch_tile_dual_k(const TileKArgs<R>& A, cplx<R>* lam, const RhoTileArgs& Q, double* partials, size_t lds,
                         hipStream_t s) {
   const uint32_t n_cosets = 1u << (A.n - A.m), threads = tile_threads_for<R, kDiag>(A.m);
@@ -631,28 +654,28 @@ void launch_tile_dual_k(const TileKArgs<R>& A, cplx<R>* lam, const RhoTileArgs& 
       static bool attr_set = false;
       static int per_cu[16] = {0};
       if (!attr_set) {
-        allow_dynamic_lds((const void*)tile_kernel_dual_pipe<R, kDiag>, kTileDynLds, "tile_pass_dual");
+        allow_dynamic_lds((const void*)tile_kernel_dual_pipe<R, kDiag, kQft>, kTileDynLds, "tile_pass_dual");
         attr_set = true;
       }
       int& nb = per_cu[A.m & 15];
       if (nb == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)tile_kernel_dual_pipe<R, kDiag>,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)tile_kernel_dual_pipe<R, kDiag, kQft>,
                                                           (int)threads, lds) != hipSuccess ||
             nb < 1)
           nb = 1;
       }
       const uint32_t grid = std::min<uint64_t>(n_cosets, (uint64_t)nb * pipe_grid(~0u));
-      QS_LAUNCH("tile_pass_dual", s, (tile_kernel_dual_pipe<R, kDiag>), dim3(grid), dim3(threads), lds, s, A, lam, Q,
+      QS_LAUNCH("tile_pass_dual", s, (tile_kernel_dual_pipe<R, kDiag, kQft>), dim3(grid), dim3(threads), lds, s, A, lam, Q,
                 partials, n_cosets);
       return;
     }
   }
   static bool attr_set = false;
   if (!attr_set) {
-    allow_dynamic_lds((const void*)tile_kernel_dual<R, kDiag>, kTileDynLds, "tile_pass_dual");
+    allow_dynamic_lds((const void*)tile_kernel_dual<R, kDiag, kQft>, kTileDynLds, "tile_pass_dual");
     attr_set = true;
   }
-  QS_LAUNCH("tile_pass_dual", s, (tile_kernel_dual<R, kDiag>), dim3(n_cosets), dim3(threads), lds, s, A, lam, Q,
+  QS_LAUNCH("tile_pass_dual", s, (tile_kernel_dual<R, kDiag, kQft>), dim3(n_cosets), dim3(threads), lds, s, A, lam, Q,
             partials);
 }
 
@@ -664,9 +687,11 @@ bool launch_tile_dual(const TileKArgs<R>& A, cplx<R>* lam, const RhoTileArgs& Q,
   for (uint32_t k = 0; k < Q.nbits; ++k)
     if (Q.tbit[k] >= A.m) return false;
   if (A.diag != nullptr)
-    launch_tile_dual_k<R, true>(A, lam, Q, partials, lds, s);
+    A.qft ? launch_tile_dual_k<R, true, 2>(A, lam, Q, partials, lds, s)
+          : launch_tile_dual_k<R, true, 0>(A, lam, Q, partials, lds, s);
   else
-    launch_tile_dual_k<R, false>(A, lam, Q, partials, lds, s);
+    A.qft ? launch_tile_dual_k<R, false, 2>(A, lam, Q, partials, lds, s)
+          : launch_tile_dual_k<R, false, 0>(A, lam, Q, partials, lds, s);
   if (Q.nbits) launch_rho_finalize(partials, 1u << (A.n - A.m), 8 * Q.nbits, out, s);
   return true;
 }
@@ -677,7 +702,9 @@ template bool launch_tile_dual<double>(const TileKArgs<double>&, cplx<double>*, 
                                        hipStream_t);
 template void launch_tile<float>(const TileKArgs<float>&, hipStream_t);
 template void launch_tile<double>(const TileKArgs<double>&, hipStream_t);
-template void launch_tile_batched<float>(const TileKArgs<float>*, uint32_t, uint32_t, uint32_t, bool, hipStream_t);
-template void launch_tile_batched<double>(const TileKArgs<double>*, uint32_t, uint32_t, uint32_t, bool, hipStream_t);
+template void launch_tile_batched<float>(const TileKArgs<float>*, uint32_t, uint32_t, uint32_t, bool, bool,
+                                         hipStream_t);
+template void launch_tile_batched<double>(const TileKArgs<double>*, uint32_t, uint32_t, uint32_t, bool, bool,
+                                         hipStream_t);
 
 }  // namespace qs

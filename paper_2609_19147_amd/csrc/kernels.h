@@ -68,6 +68,7 @@ struct TileKArgs {
                       // of all XCDs on neighbouring cosets)
   uint32_t keep;      // for the launcher, complex64: 1 cached accesses to psi
                       // (keep_resident), 0 streaming
+  uint32_t qft;       // for the launcher: 1 the pass has QFT stages, 2 some in chains
 };
 template <class R> void launch_tile(const TileKArgs<R>& A, hipStream_t s);
 // Fused adjoint step (declared here, RhoTileArgs below): the pass A undone on
@@ -83,10 +84,10 @@ template <class R>
 bool launch_tile_dual(const TileKArgs<R>& A, cplx<R>* lam, const RhoTileArgs& Q, double* partials, double* out,
                       hipStream_t s);
 // count instances of one geometry (n qubits, m tile bits), descriptors in device
-// memory; has_diag: some descriptor has a diagonal slot.
+// memory; has_diag: some descriptor has a diagonal slot, has_qft: a QFT stage.
 template <class R>
 void launch_tile_batched(const TileKArgs<R>* descs_dev, uint32_t count, uint32_t n, uint32_t m, bool has_diag,
-                         hipStream_t s);
+                         bool has_qft, hipStream_t s);
 
 // One layer of a state of a single tile (k_seq.hip): a tile pass over all n bits
 // (n_rounds > 0), or a GF(2) gather out[y] = in[A y ^ cprime], acol[j] = A e_j.

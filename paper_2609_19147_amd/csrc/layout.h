@@ -94,6 +94,11 @@ enum TileRoundType : int32_t {
   RT_ZYZ4 = 18,
   RT_YZ4 = 19,
   RT_ZY4 = 20,
+  // device only: neighbouring RT_QFT1, RT_QH1, RT_OP1 and Hadamard-only RT_MAT4
+  // rounds over the same register bits (what the planner split from one round),
+  // their ops run one after the other on the registers: one pass over the tile
+  // instead of one each
+  RT_CHAIN = 21,
 };
 // The planner splits a round matching none of the patterns into a sequence of
 // rounds over the same register bits (RT_MAT4 groups and RT_QFT1 stages).

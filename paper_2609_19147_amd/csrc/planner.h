@@ -103,6 +103,12 @@ struct TilePassIR {
   double scale = 1.0;       // 2^(-n_butterfly/2), applied at the store
   bool inverse = false;     // ops are inverses of their sources (U^dagger, QFT^-1, conj diagonals)
 };
+// Does the pass have a QFT (or inverse QFT) stage?
+inline bool pass_has_qft(const TilePassIR& T) {
+  for (const TileOp& op : T.ops)
+    if (op.kind == OP_QFT || op.kind == OP_QFT_INV) return true;
+  return false;
+}
 
 struct Gf2IR {
   std::vector<uint32_t> rows;  // A rows: src bit r = parity(rows[r] & y)

@@ -165,6 +165,52 @@ void round_pass_unitaries(const TilePassIR& T, const std::vector<TileRound>& rou
   }
 }
 
+// Neighbouring rounds over the same register bits, QFT stages among them, become
+// one RT_CHAIN where the kernel has no straight-line code for them: each round
+// less is a read and a write of the tile in LDS and a barrier less (27-qubit
+// complex128 QFT and Walsh passes of five rounds over two sets of bits: 1120 us
+// each, as two rounds 920).  A Hadamard moves up to the last op before it that acts
+// on its bit or reads it: right behind its QFT stage the two run as one.
+void chain_rounds(std::vector<TileRound>& rounds, std::vector<TileOp>& ops) {
+  auto stage = [&](int k) { return ops[k].kind == OP_QFT || ops[k].kind == OP_QFT_INV; };
+  auto chainable = [&](const TileRound& r) {
+    if (r.type == RT_QFT1 || r.type == RT_QH1 || r.type == RT_OP1) return true;
+    if (r.type != RT_MAT4) return false;
+    for (int k = r.op_begin; k < r.op_end; ++k)
+      if (ops[k].kind != OP_H) return false;
+    return true;
+  };
+  std::vector<TileRound> out;
+  for (size_t i = 0; i < rounds.size();) {
+    TileRound r = rounds[i];
+    size_t j = i + 1;
+    if (chainable(r)) {
+      while (j < rounds.size() && chainable(rounds[j]) && rounds[j].op_begin == r.op_end &&
+             std::equal(r.tbit, r.tbit + kRoundBits, rounds[j].tbit))
+        r.op_end = rounds[j++].op_end;
+    }
+    bool any = false;
+    for (int k = r.op_begin; k < r.op_end; ++k) any = any || stage(k);
+    if (j == i + 1 || !any) {
+      out.push_back(rounds[i++]);
+      continue;
+    }
+    r.type = RT_CHAIN;
+    for (int k = r.op_begin + 1; k < r.op_end; ++k) {
+      if (ops[k].kind != OP_H) continue;
+      for (int t = k; t > r.op_begin; --t) {
+        const TileOp& o = ops[t - 1];
+        const bool reads = stage(t - 1) && o.sbit > ops[t].sbit && o.base <= ops[t].sbit;
+        if (o.sbit == ops[t].sbit || reads) break;
+        std::swap(ops[t - 1], ops[t]);
+      }
+    }
+    out.push_back(r);
+    i = j;
+  }
+  rounds.swap(out);
+}
+
 template <class R>
 void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
   const PlanIR& P = p.ir;
@@ -194,6 +240,7 @@ void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
   d.pass_diag.assign(P.passes.size(), 0);
   d.pass_qtab.assign(P.passes.size(), 0);
   d.pass_nrounds.assign(P.passes.size(), 0);
+  d.pass_qft.assign(P.passes.size(), 0);
   d.pass_scale.assign(P.passes.size(), 1.0);
   for (size_t i = 0; i < P.passes.size(); ++i) {
     const TilePassIR& T = P.passes[i];
@@ -250,7 +297,12 @@ void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
       r.diag = -1;
       rounds.push_back(r);
     }
+    std::vector<TileOp> ops = T.ops;
+    chain_rounds(rounds, ops);
     d.pass_nrounds[i] = (uint32_t)rounds.size();
+    d.pass_qft[i] = pass_has_qft(T);
+    for (const TileRound& r : rounds)
+      if (r.type == RT_CHAIN) d.pass_qft[i] = 2;
     // Rotation rounds (RX / RY, alone or after a pair diagonal) whose four
     // matrices all have |b| <= 8 |a| run factored: [[a, -i b], [-i b, a]] =
     // a [[1, -i t], [-i t, 1]] with t = b / a (RY alike), one multiply-add
@@ -330,7 +382,7 @@ void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
     }
     if (!qtab.empty()) d.pass_qtab[i] = b.put(qtab);
     d.pass_rounds[i] = b.put(rounds);
-    d.pass_ops[i] = b.put(T.ops);
+    d.pass_ops[i] = b.put(ops);
     std::vector<cplx<R>> cr = round_entries<R>(coef);
     if (sizeof(R) == sizeof(float)) round_pass_unitaries(T, rounds, coef, cr, acc);
     for (int32_t k : rot_coef) cr[k] = {(R)coef[k].real(), (R)coef[k].imag()};
@@ -619,6 +671,7 @@ TileKArgs<R> tile_args(qs_state& s, qs_plan& p, int pass) {
   A.n = s.n;
   A.scale = d.pass_scale[pass];
   A.keep = keep_resident(s.state_bytes(), kTileResidentFrom);
+  A.qft = d.pass_qft[pass];
   return A;
 }
 template TileKArgs<float> tile_args<float>(qs_state&, qs_plan&, int);

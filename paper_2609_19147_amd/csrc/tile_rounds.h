@@ -304,6 +304,52 @@ struct FQft1 {
   }
 };
 
+// Any sequence of ops on the round's register bits, one after the other on the
+// registers (RT_CHAIN).  A QFT stage and the Hadamard
+// of its bit behind it run as one; every stage evaluates its twiddle.
+template <class R>
+struct FChain {
+  cptr<TileOp> ops;
+  int n;
+  cptr<cplx<R>> coef;
+  template <int S>
+  __device__ __forceinline__ static void run(cplx<R>* a, int kind, cplx<R> w, cptr<cplx<R>> c) {
+    switch (kind) {
+      case OP_H: op_h<S>(a); break;
+      case OP_DIAG: op_diag<S>(a, c); break;
+      case OP_QFT: op_qft<S, R, false>(a, w, c); break;
+      case OP_QFT_INV: op_qft<S, R, true>(a, w, c); break;
+      case kQftH: op_qft<S, R, false, true>(a, w, c); break;
+      default: op_mat<S>(a, c); break;
+    }
+  }
+  static constexpr int kQftH = -1;
+  __device__ __forceinline__ void operator()(cplx<R>* a, uint32_t g) const {
+#pragma unroll 1
+    for (int k = 0; k < n;) {
+      const cptr<TileOp> op = ops + k;
+      const int rbit = op->rbit;
+      int kind = op->kind, step = 1;
+      cplx<R> w = {R(1), R(0)};
+      if (kind == OP_QFT || kind == OP_QFT_INV) {
+        w = cispi<R>(stage_low(g, op->sbit, op->base), op->sbit);
+        if (kind == OP_QFT && k + 1 < n && op[1].kind == OP_H && op[1].rbit == rbit) {
+          kind = kQftH;
+          step = 2;
+        }
+      }
+      const cptr<cplx<R>> c = coef + op->coef;
+      switch (rbit & 3) {
+        case 0: run<0>(a, kind, w, c); break;
+        case 1: run<1>(a, kind, w, c); break;
+        case 2: run<2>(a, kind, w, c); break;
+        default: run<3>(a, kind, w, c); break;
+      }
+      k += step;
+    }
+  }
+};
+
 // Diagonal slot d of a pass (uniform): its descriptor read with scalar loads.
 __device__ __forceinline__ DiagDev diag_slot(const DiagDev* slots, int d) {
   const cptr<DiagDev> S = to_const(slots) + d;
@@ -465,8 +511,10 @@ __device__ __forceinline__ Ctx coset_ctx(const TileKArgs<R>& A, uint32_t coset) 
   return C;
 }
 
-// kTwo: the rounds run on T and T1 together (RoundLoop2).
-template <class R, bool kDiag, bool kTwo = false>
+// kTwo: the rounds run on T and T1 together (RoundLoop2).  kQft: 0 the pass
+// has no QFT stages and their code is left out, 1 it has, none in an RT_CHAIN,
+// 2 any (rounds of one stage run as chains of one).
+template <class R, bool kDiag, bool kTwo = false, int kQft = 2>
 __device__ __forceinline__ void tile_rounds(const TileKArgs<R>& A, const Ctx& C, cplx<R>* T, uint32_t nthr,
                                             uint32_t tid, cplx<R>* T1 = nullptr) {
   // threads tid < nthr take the register groups; every thread of the workgroup
@@ -525,16 +573,16 @@ __device__ __forceinline__ void tile_rounds(const TileKArgs<R>& A, const Ctx& C,
         }
         break;
       case RT_QFT4:
-        L(FQft4<R, false, false>{ops + R_->op_begin, coef});
+        if constexpr (kQft > 0) L(FQft4<R, false, false>{ops + R_->op_begin, coef});
         break;
       case RT_QFT4_H4:
-        L(FQft4<R, true, false>{ops + R_->op_begin, coef});
+        if constexpr (kQft > 0) L(FQft4<R, true, false>{ops + R_->op_begin, coef});
         break;
       case RT_QFT4S:
-        L(FQft4<R, false, true>{ops + R_->op_begin, coef});
+        if constexpr (kQft > 0) L(FQft4<R, false, true>{ops + R_->op_begin, coef});
         break;
       case RT_QFT4S_H4:
-        L(FQft4<R, true, true>{ops + R_->op_begin, coef});
+        if constexpr (kQft > 0) L(FQft4<R, true, true>{ops + R_->op_begin, coef});
         break;
       case RT_H4:
         L(FH4<R>{});
@@ -583,34 +631,41 @@ __device__ __forceinline__ void tile_rounds(const TileKArgs<R>& A, const Ctx& C,
         }
         break;
       }
-      case RT_QH1: {
-        const cptr<TileOp> op = ops + R_->op_begin;
-        const cptr<cplx<R>> E = coef + op->coef;
-        const int p = op->sbit, base = op->base;
-        switch (op->rbit & 3) {
-          case 0: L(FQft1<0, R, true, false>{E, p, base}); break;
-          case 1: L(FQft1<1, R, true, false>{E, p, base}); break;
-          case 2: L(FQft1<2, R, true, false>{E, p, base}); break;
-          default: L(FQft1<3, R, true, false>{E, p, base}); break;
+      case RT_QH1:
+        if constexpr (kQft == 1) {
+          const cptr<TileOp> op = ops + R_->op_begin;
+          const cptr<cplx<R>> E = coef + op->coef;
+          const int p = op->sbit, base = op->base;
+          switch (op->rbit & 3) {
+            case 0: L(FQft1<0, R, true, false>{E, p, base}); break;
+            case 1: L(FQft1<1, R, true, false>{E, p, base}); break;
+            case 2: L(FQft1<2, R, true, false>{E, p, base}); break;
+            default: L(FQft1<3, R, true, false>{E, p, base}); break;
+          }
+          break;
         }
-        break;
-      }
-      default: {  // RT_QFT1
-        const cptr<TileOp> op = ops + R_->op_begin;
-        const cptr<cplx<R>> E = coef + op->coef;
-        const int p = op->sbit, base = op->base;
-        switch ((op->kind == OP_QFT_INV ? 4 : 0) + (op->rbit & 3)) {
-          case 0: L(FQft1<0, R, false, false>{E, p, base}); break;
-          case 1: L(FQft1<1, R, false, false>{E, p, base}); break;
-          case 2: L(FQft1<2, R, false, false>{E, p, base}); break;
-          case 3: L(FQft1<3, R, false, false>{E, p, base}); break;
-          case 4: L(FQft1<0, R, false, true>{E, p, base}); break;
-          case 5: L(FQft1<1, R, false, true>{E, p, base}); break;
-          case 6: L(FQft1<2, R, false, true>{E, p, base}); break;
-          default: L(FQft1<3, R, false, true>{E, p, base}); break;
+        [[fallthrough]];
+      case RT_QFT1:
+        if constexpr (kQft == 1) {
+          const cptr<TileOp> op = ops + R_->op_begin;
+          const cptr<cplx<R>> E = coef + op->coef;
+          const int p = op->sbit, base = op->base;
+          switch ((op->kind == OP_QFT_INV ? 4 : 0) + (op->rbit & 3)) {
+            case 0: L(FQft1<0, R, false, false>{E, p, base}); break;
+            case 1: L(FQft1<1, R, false, false>{E, p, base}); break;
+            case 2: L(FQft1<2, R, false, false>{E, p, base}); break;
+            case 3: L(FQft1<3, R, false, false>{E, p, base}); break;
+            case 4: L(FQft1<0, R, false, true>{E, p, base}); break;
+            case 5: L(FQft1<1, R, false, true>{E, p, base}); break;
+            case 6: L(FQft1<2, R, false, true>{E, p, base}); break;
+            default: L(FQft1<3, R, false, true>{E, p, base}); break;
+          }
+          break;
         }
+        [[fallthrough]];
+      default:  // RT_CHAIN
+        if constexpr (kQft == 2) L(FChain<R>{ops + R_->op_begin, R_->op_end - R_->op_begin, coef});
         break;
-      }
     }
     __syncthreads();
   }
