@@ -1338,8 +1338,16 @@ void finalize_pass(const PlanIR& P, TilePassIR& T) {
     TileRound r;
     std::memset(&r, 0, sizeof r);
     r.qoff = -1;
-    for (int tb = 0; (int)bits.size() < RB && tb < m; ++tb)
-      if (std::find(bits.begin(), bits.end(), tb) == bits.end()) bits.push_back(tb);
+    // spare register bits: the free tile bits next below the round's top one, then
+    // the next above.  A wavefront's lanes are the lowest tile bits that no
+    // register has: with low spares (0, 1) they were two or four elements apart
+    // in LDS, two lanes to a bank, now they are neighbours.
+    const int top = bits.empty() ? m : *std::max_element(bits.begin(), bits.end());
+    auto spare = [&](int tb) {
+      if ((int)bits.size() < RB && std::find(bits.begin(), bits.end(), tb) == bits.end()) bits.push_back(tb);
+    };
+    for (int tb = top - 1; tb >= 0; --tb) spare(tb);
+    for (int tb = top + 1; tb < m; ++tb) spare(tb);
     std::sort(bits.begin(), bits.end());
     for (int k = 0; k < RB; ++k) r.tbit[k] = bits[k];
     for (int j = 0; j < (1 << RB); ++j) {
