@@ -26,14 +26,15 @@
 // What bounds them: HBM, and for k = 6 (complex128 also k = 5) the matrix cores.
 // Address arithmetic is kept off the tile loop (it cost up to a third of it): a
 // thread's state and LDS offsets are a lane part plus uniform parts, held in
-// registers.  us per block at the start of the tile loop's rework, and now:
+// registers.  us per block with FP32 products for complex64 k = 5 and 6, deposits
+// and tables in the tile loop and 2048 workgroups, and now:
 //             complex64                      complex128
 //   n      k=4       k=5       k=6       k=4       k=5        k=6
 //   16   5.6 4.7   8.0 6.5  15.2  9.5  6.2 5.2  10.0 7.6   20.4 13.7
-//   22    18  14    29  17    40   23    28  23    45  32     83   51
-//   25    88  73   100  79   157  115   210 183   249 196    454  316
-//   27   426 370   438 355   679  464   865 756   942 809   1646 1227
-// (27 qubits complex64: 2.1 GB moved, 5.8, 6.0 and 4.6 TB/s; a copy of this
+//   22    18  14    29  18    40   23    28  22    45  32     83   51
+//   25   106  73   122  79   195  128   210 183   249 195    454  312
+//   27   426 371   438 360   679  445   865 756   942 805   1646 1206
+// (27 qubits complex64: 2.1 GB moved, 5.8, 6.0 and 4.8 TB/s; a copy of this
 // size reaches 5.65.)
 //
 // Operand layouts of V_MFMA_{F32,F64}_16X16X4 (wave64): A[i][kk] in lane
@@ -254,13 +255,14 @@ dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_, DenseGeom G) {
 // U X = sum_ij U_i X_j with every product exact in the FP32 accumulators; the six
 // products with i + j <= 4 are taken, the three left out are below 2^-24 of
 // |u| |x| in all and of random sign.  Six bf16 products cost 6 / 16 of an FP32
-// one, and 32 of them enter an accumulator per instruction instead of 4, so fewer
-// sums are rounded: against complex128, the error of a block (amplitudes of
-// unit size, 9 to 20 qubits) is 0.78e-7 rms and 10.4e-7 at most for k = 5 and
-// 1.30e-7 and 17.2e-7 for k = 6, with the FP32 forms 1.48e-7 and 15.1e-7, and
-// 2.05e-7 and 24.1e-7; after 40 blocks 4.9e-7 and 8.2e-7 rms against 9.2e-7 and
-// 13.0e-7.  k = 5 is then bound by HBM, k = 6 by the
-// bf16 products and the splitting of X (each about 160 us of the 464).
+// one, and 32 of them enter an accumulator per instruction instead of 4.
+// Error against complex128, FP32 forms and now: one random block (9 to 20
+// qubits, amplitudes of unit size) k = 5 1.48e-7 rms, 0.55e-7 now (15.1e-7 at
+// most, 5.5e-7), k = 6 2.05e-7, 1.17e-7 (24.1e-7, 16.3e-7); 40 windows within
+// 1e-3 of the identity 9.5e-7, 6.2e-7 and 13.2e-7, 8.8e-7; five steps of a
+// 20-qubit ladder 4.4e-7, 3.5e-7; a 23-qubit transform circuit in windows 3.3e-7,
+// 2.6e-7 (largest 2.2e-6, 1.7e-6).  k = 5 is then bound by HBM, k = 6 by the
+// bf16 products and the splitting of X (each about 160 us of the 445) as well.
 // V_MFMA_F32_16X16X32_BF16: lane l holds row (A) or column (B) l % 16 and the
 // eight depths of its quarter l / 16 (A and B alike, so the contraction does not
 // depend on their order); D as for the FP32 16x16 forms.
@@ -290,18 +292,26 @@ __device__ __forceinline__ void split8(const float (&x)[8], Split8& S) {
   S.m = __builtin_bit_cast(bf16x8, m);
   S.l = __builtin_bit_cast(bf16x8, l);
 }
+__device__ __forceinline__ void negate(Split8& S) {
+  S.h = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.h) ^ 0x80008000u);
+  S.m = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.m) ^ 0x80008000u);
+  S.l = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.l) ^ 0x80008000u);
+}
 __device__ __forceinline__ f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// c + a b, the small products first.
-__device__ __forceinline__ f32x4 mfma_split(const Split8& a, const Split8& b, f32x4 c) {
+// c + a b in two parts, the small products and the large one.  The sums are
+// rounded at the size of what they have reached, so a block adds all of its
+// small products first, and those of Ui, the smaller part of the common windows
+// near the identity, before Ur's.
+__device__ __forceinline__ f32x4 mfma_small(const Split8& a, const Split8& b, f32x4 c) {
   c = mfma_bf16(a.l, b.h, c);
   c = mfma_bf16(a.h, b.l, c);
   c = mfma_bf16(a.m, b.m, c);
   c = mfma_bf16(a.m, b.h, c);
-  c = mfma_bf16(a.h, b.m, c);
-  return mfma_bf16(a.h, b.h, c);
+  return mfma_bf16(a.h, b.m, c);
 }
+__device__ __forceinline__ f32x4 mfma_large(const Split8& a, const Split8& b, f32x4 c) { return mfma_bf16(a.h, b.h, c); }
 
 // The finite floats from here on round to infinity in bf16, and an infinity's
 // remainder is no number: such a block takes the FP32 forms.
@@ -321,7 +331,7 @@ template <int K>
 __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(K == 64 ? 2 : 3)))
 dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGeom G) {
   constexpr int kSlabs = K / 32, RT = 2;
-  constexpr bool kPair = K == 64;
+  constexpr bool kPair = K == 64, kOwnSmall = K == 32;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<float>* T = reinterpret_cast<cplx<float>*>(smem_raw);
   uint32_t* unfit = reinterpret_cast<uint32_t*>(smem_raw + sizeof(cplx<float>) * dense_lds_off(1u << G.m));
@@ -357,8 +367,26 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
   const uint32_t wr = B.col_lane(li) + B.rows(lk, 2, 2) + (rt0 ? B.row[5] : 0u);
   const uint32_t ncb = (1u << G.c) >> 4;
   const uint32_t trips = (ncb + cbs - 1u) / cbs;  // uniform: barriers inside
+  float sgn = 1.0f;
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
     const uint32_t base = dense_tile_base(t, G);
+    // Half of the column blocks, picked by a hash, are multiplied by -U and negated:
+    // the bf16 matrix cores round sums down, and with one sign every amplitude of a
+    // state would carry an error of the same direction (a transform circuit of
+    // dense windows on 20 qubits: 5.6e-5 of a mean amplitude in one output instead
+    // of 2e-6).
+    uint32_t hash = (4u * t + cb0) * 0x85ebca6bu;
+    hash = (hash ^ (hash >> 13)) * 0xc2b2ae35u;
+    if ((hash >> 31 ? -1.0f : 1.0f) != sgn) {
+      sgn = -sgn;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int sl = 0; sl < kSlabs; ++sl) {
+          negate(ur[rt][sl]);
+          negate(ui[rt][sl]);
+        }
+    }
     if constexpr (kPair) {
       io.put(T, pre);
       if (t + gridDim.x < G.n_tiles) io.issue(G.keep, dense_tile_base(t + gridDim.x, G), pre);
@@ -370,9 +398,11 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
       const uint32_t cb = cb0 + it * cbs;
       const bool on = cb < ncb;
       const uint32_t colp = B.col_block(cb);
-      f32x4 rr[RT], ii[RT], ri[RT];  // Ur Xr, Ui Xi, Ur Xi + Ui Xr
+      // Ur Xr, Ui Xi, Ur Xi + Ui Xr: the large products and, k = 5, the small ones
+      // by themselves (k = 6: 24 more registers spill, 441 -> 555 us at 27 qubits)
+      f32x4 rr[RT], ii[RT], ri[RT], srr[RT], sii[RT], sri[RT];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) rr[rt] = ii[rt] = ri[rt] = f32x4{0, 0, 0, 0};
+      for (int rt = 0; rt < RT; ++rt) rr[rt] = ii[rt] = ri[rt] = srr[rt] = sii[rt] = sri[rt] = f32x4{0, 0, 0, 0};
       if (on) {
 #pragma unroll
         for (int sl = 0; sl < kSlabs; ++sl) {
@@ -389,10 +419,18 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
           split8(im, xi);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
-            rr[rt] = mfma_split(ur[rt][sl], xr, rr[rt]);
-            ii[rt] = mfma_split(ui[rt][sl], xi, ii[rt]);
-            ri[rt] = mfma_split(ur[rt][sl], xi, ri[rt]);
-            ri[rt] = mfma_split(ui[rt][sl], xr, ri[rt]);
+            f32x4& a = kOwnSmall ? srr[rt] : rr[rt];
+            f32x4& b = kOwnSmall ? sii[rt] : ii[rt];
+            f32x4& c = kOwnSmall ? sri[rt] : ri[rt];
+            a = mfma_small(ur[rt][sl], xr, a);
+            b = mfma_small(ui[rt][sl], xi, b);
+            c = mfma_small(ur[rt][sl], xi, mfma_small(ui[rt][sl], xr, c));
+          }
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            rr[rt] = mfma_large(ur[rt][sl], xr, rr[rt]);
+            ii[rt] = mfma_large(ui[rt][sl], xi, ii[rt]);
+            ri[rt] = mfma_large(ur[rt][sl], xi, mfma_large(ui[rt][sl], xr, ri[rt]));
           }
         }
       }
@@ -402,7 +440,10 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
-            T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] = cplx<float>{rr[rt][v] - ii[rt][v], ri[rt][v]};
+            T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] =
+                kOwnSmall ? cplx<float>{sgn * ((rr[rt][v] - ii[rt][v]) + (srr[rt][v] - sii[rt][v])),
+                                        sgn * (ri[rt][v] + sri[rt][v])}
+                          : cplx<float>{sgn * (rr[rt][v] - ii[rt][v]), sgn * ri[rt][v]};
       }
     }
     if (__any(xmax >= kSplitMax) && lane == 0) *unfit = 1u;  // and so for the tiles that follow

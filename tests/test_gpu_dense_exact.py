@@ -81,6 +81,27 @@ def test_complex64_error_against_complex128(k, n):
     assert rms <= np.sqrt(4 * (1 << k) / 2 / 3) * 2.0 ** -24, rms
 
 
+@pytest.mark.parametrize("k", [5, 6])
+def test_complex64_errors_have_no_common_direction(k):
+    import torch
+    import paper_2609_19147_amd as qs
+    n = 22
+    rng = np.random.default_rng(k)
+    h = W.random_unitary(1 << k, rng)
+    m, _ = np.linalg.qr(np.eye(1 << k) + 0.02 * (h - h.conj().T))
+    a = _state(qs, n, "c64", n)
+    b = qs.State(n, "c128", init=None)
+    b.tensor().copy_(a.tensor())
+    plan = qs.Plan(n, [W.G("UNITARY", *_wires(n, k, rng), mat=m)])
+    qs.apply(a, plan)
+    qs.apply(b, plan)
+    err = a.tensor().to(torch.complex128) - b.tensor()
+    # the 16 2^k amplitudes of a column block may share a direction, the blocks
+    # are independent: six standard deviations of their sum
+    bound = 6 * np.sqrt((1 << n) * 16 * (1 << k)) * err.abs().pow(2).mean().sqrt().item()
+    assert abs(err.sum().item()) <= bound
+
+
 @pytest.mark.parametrize("big", [np.float32(3.4e38), np.float32(np.inf)])
 @pytest.mark.parametrize("k,n", [(5, 9), (5, 14), (6, 10), (6, 14)])
 def test_values_beyond_bf16(k, n, big):
