@@ -92,7 +92,7 @@ def circuit(n):
 
 
 def kernel_source_hash(kernel: str) -> str:
-    files = {"tile_pass": ["k_tile.hip", "dev.h", "layout.h", "kernels.h"],
+    files = {"tile_pass": ["k_tile.hip", "tile_rounds.h", "dev.h", "layout.h", "kernels.h"],
              "gf2_gather": ["k_stream.hip", "dev.h", "layout.h", "kernels.h"]}[kernel]
     h = hashlib.sha256()
     for f in files:
