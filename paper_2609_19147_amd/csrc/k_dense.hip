@@ -42,6 +42,7 @@
 // register i % 4 for F32, and in lane j + 16 (i % 4), register i / 4 for F64
 // (checked by a one-hot probe of both builtins).
 #include "kernels.h"
+#include "lanes.h"
 
 #include <type_traits>
 
@@ -249,29 +250,42 @@ dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_, DenseGeom G) {
 }
 
 // ---- complex64 k = 5 and 6 on the bf16 matrix cores ----------------------------
-// The FP32 matrix cores make k = 5 and 6 compute-bound (27 qubits: 438 and 679 us
-// against the 380 us that the state's traffic takes).  A float is the exact sum
-// of three bf16 numbers (8 significant bits each, signs absorbing the rest), so
-// U X = sum_ij U_i X_j with every product exact in the FP32 accumulators; the six
-// products with i + j <= 4 are taken, the three left out are below 2^-24 of
-// |u| |x| in all and of random sign.  Six bf16 products cost 6 / 16 of an FP32
-// one, and 32 of them enter an accumulator per instruction instead of 4.
-// Error against complex128, FP32 forms and now: one random block (9 to 20
-// qubits, amplitudes of unit size) k = 5 1.48e-7 rms, 0.55e-7 now (15.1e-7 at
-// most, 5.5e-7), k = 6 2.05e-7, 1.17e-7 (24.1e-7, 16.3e-7); 40 windows within
-// 1e-3 of the identity 9.5e-7, 6.2e-7 and 13.2e-7, 8.8e-7; five steps of a
-// 20-qubit ladder 4.4e-7, 3.5e-7; a 23-qubit transform circuit in windows 3.3e-7,
-// 2.6e-7 (largest 2.2e-6, 1.7e-6).  k = 5 is then bound by HBM, k = 6 by the
-// bf16 products and the splitting of X (each about 160 us of the 445) as well.
+// The FP32 matrix cores make k = 6 compute-bound (27 qubits, this tile loop: 575
+// us, against the 380 that the state's traffic takes) and k = 5 nearly so (405).
+// A float is the exact sum h + m + l of three bf16 numbers (8 significant bits
+// each, signs absorbing the rest), so U X = sum_ij U_i X_j with products that are
+// exact in FP32; the six with i + j <= 4 are taken, the three left out are below
+// 2^-24 of |u| |x| in all and of random sign.  Six bf16 products cost 6 / 16 of
+// an FP32 one, and 32 of them enter an accumulator per instruction instead of 4.
+//
 // V_MFMA_F32_16X16X32_BF16: lane l holds row (A) or column (B) l % 16 and the
 // eight depths of its quarter l / 16 (A and B alike, so the contraction does not
-// depend on their order); D as for the FP32 16x16 forms.
+// depend on their order); D as for the FP32 16x16 forms.  What it rounds (probed
+// with single products): a quarter's eight products are cut, towards zero, at
+// 2^-24 of the largest one and added; the sum enters the accumulator with one
+// rounding to nearest, a smaller accumulator first being cut there too, downwards.
+// Beside a product with an entry of U near one, those with U's small entries so
+// lose their last bits, and with the same sign each time: a window near the
+// identity, applied again and again as Trotter steps do, had an error that grew
+// with the number of steps.  U's heads h are therefore taken in two, the large
+// ones (from an eighth of U's largest entry on) and the others, each with
+// products, and the large ones with accumulators, of their own: seven products.
+//
+// Error (2-norm) against complex128, FP32 forms, six products, now, for 1, 40 and
+// 400 applications, 1e-7:
+//   k = 5  window within 1e-3 of 1   1.5  17  91   0.9  25  233   0.3  7.3  71
+//          random unitary            1.5 9.3  34   0.5 3.7   21   0.5  3.1  20
+//   k = 6  window within 1e-3 of 1   2.1  26 119   1.2  31  265   0.3  7.0  68
+//          random unitary            2.0  13  43   1.2 7.4   26   0.6  3.6  16
+// (what is left near the identity is U's rounding to float).  27 qubits: k = 5 385
+// us with six products, 388 now, k = 6 482 and 524.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// x = h + m + l, eight numbers at a time (converted in pairs).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// x = h + m + l, eight numbers at a time (converted in pairs).
 struct Split8 {
   bf16x8 h, m, l;
 };
@@ -292,30 +306,44 @@ __device__ __forceinline__ void split8(const float (&x)[8], Split8& S) {
   S.m = __builtin_bit_cast(bf16x8, m);
   S.l = __builtin_bit_cast(bf16x8, l);
 }
+// U's numbers: h in two, the large ones (from `large` on) and the others.
+struct SplitU8 {
+  u32x4 big, rest, m, l;
+  __device__ __forceinline__ SplitU8() = default;
+  __device__ __forceinline__ SplitU8(const float (&u)[8], float large) {
+    Split8 S;
+    split8(u, S);
+    const u32x4 h = __builtin_bit_cast(u32x4, S.h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t keep = (fabsf(u[2 * e]) >= large ? 0xffffu : 0u) | (fabsf(u[2 * e + 1]) >= large ? 0xffff0000u : 0u);
+      big[e] = h[e] & keep;
+      rest[e] = h[e] & ~keep;
+    }
+    m = __builtin_bit_cast(u32x4, S.m);
+    l = __builtin_bit_cast(u32x4, S.l);
+  }
+  // h, put together where it is used: `never`, a zero that the compiler cannot know,
+  // keeps it from holding h in registers as well
+  __device__ __forceinline__ u32x4 head(uint32_t never) const { return (big ^ never) | rest; }
+};
+__device__ __forceinline__ f32x4 mfma_bf16(const u32x4& a, const bf16x8& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, c, 0, 0, 0);
+}
 __device__ __forceinline__ void negate(Split8& S) {
   S.h = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.h) ^ 0x80008000u);
   S.m = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.m) ^ 0x80008000u);
   S.l = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.l) ^ 0x80008000u);
 }
-__device__ __forceinline__ f32x4 mfma_bf16(const bf16x8& a, const bf16x8& b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+// A lane mask folded over the four lanes l, l + 16, ... of a column: 16 bits.
+__device__ __forceinline__ uint32_t fold_xor16(uint64_t m) {
+  const uint32_t w = (uint32_t)m ^ (uint32_t)(m >> 32);
+  return w ^ w >> 16;
 }
-// c + a b in two parts, the small products and the large one.  The sums are
-// rounded at the size of what they have reached, so a block adds all of its
-// small products first, and those of Ui, the smaller part of the common windows
-// near the identity, before Ur's.
-__device__ __forceinline__ f32x4 mfma_small(const Split8& a, const Split8& b, f32x4 c) {
-  c = mfma_bf16(a.l, b.h, c);
-  c = mfma_bf16(a.h, b.l, c);
-  c = mfma_bf16(a.m, b.m, c);
-  c = mfma_bf16(a.m, b.h, c);
-  return mfma_bf16(a.h, b.m, c);
-}
-__device__ __forceinline__ f32x4 mfma_large(const Split8& a, const Split8& b, f32x4 c) { return mfma_bf16(a.h, b.h, c); }
-
 // The finite floats from here on round to infinity in bf16, and an infinity's
-// remainder is no number: such a block takes the FP32 forms.
+// remainder is no number: such a tile takes the FP32 forms.
 constexpr float kSplitMax = 0x1.ffp127f;
+constexpr float kLargeU = 0x1p-3f;  // of U's largest entry
 // max(m, |a|, |b|) in one instruction (fmaxf first canonicalises each operand)
 __device__ __forceinline__ float max3_abs(float m, float a, float b) {
   asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
@@ -326,12 +354,12 @@ __device__ __forceinline__ float max3_abs(float m, float a, float b) {
 // four 16-row tiles, with a barrier between a block's reads and its in-place
 // writes; k = 5: a wave takes whole column blocks.  At k = 6 the next tile's
 // loads are issued before this tile's contraction (two waves per SIMD hold them
-// and U's split fragments; three spill).
+// and U's parts; three spill).
 template <int K>
 __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(K == 64 ? 2 : 3)))
 dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGeom G) {
   constexpr int kSlabs = K / 32, RT = 2;
-  constexpr bool kPair = K == 64, kOwnSmall = K == 32;
+  constexpr bool kPair = K == 64;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cplx<float>* T = reinterpret_cast<cplx<float>*>(smem_raw);
   uint32_t* unfit = reinterpret_cast<uint32_t*>(smem_raw + sizeof(cplx<float>) * dense_lds_off(1u << G.m));
@@ -340,53 +368,45 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
   const uint32_t li = lane & 15u, lk = lane >> 4;
   const uint32_t rt0 = kPair ? 2u * (wave & 1u) : 0u;
   const uint32_t cb0 = kPair ? wave >> 1 : wave, cbs = kPair ? 2u : 4u;
-  if (threadIdx.x == 0) *unfit = 0u;
   const DenseIO<float, 2, K / 8, kDenseThreads> io(psi, G);
   cplx2<float> pre[K / 8];
   if (kPair && blockIdx.x < G.n_tiles) io.issue(G.keep, dense_tile_base(blockIdx.x, G), pre);
-  Split8 ur[RT][kSlabs], ui[RT][kSlabs];
-  float xmax = 0.0f;
+  SplitU8 ur[RT][kSlabs], ui[RT][kSlabs];
+  bool u_unfit;
+  {
+    float re[RT][kSlabs][8], im[RT][kSlabs][8], m = 0.0f;
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int sl = 0; sl < kSlabs; ++sl) {
-      const cplx<float>* u = U_ + (16u * (rt0 + rt) + li) * K + 32u * sl + 8u * lk;
-      float re[8], im[8];
+      for (int sl = 0; sl < kSlabs; ++sl) {
+        const cplx<float>* u = U_ + (16u * (rt0 + rt) + li) * K + 32u * sl + 8u * lk;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        re[e] = u[e].re;
-        im[e] = u[e].im;
-        xmax = max3_abs(xmax, re[e], im[e]);
+        for (int e = 0; e < 8; ++e) {
+          re[rt][sl][e] = u[e].re;
+          im[rt][sl][e] = u[e].im;
+          m = max3_abs(m, re[rt][sl][e], im[rt][sl][e]);
+        }
       }
-      split8(re, ur[rt][sl]);
-      split8(im, ui[rt][sl]);
-    }
+    m = wave_max(m);
+    u_unfit = m >= kSplitMax;
+    const float large = m * kLargeU;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int sl = 0; sl < kSlabs; ++sl) {
+        ur[rt][sl] = SplitU8(re[rt][sl], large);
+        ui[rt][sl] = SplitU8(im[rt][sl], large);
+      }
+  }
   // rows a lane reads, 32 sl + 8 lk + e, and writes, 16 (rt0 + rt) + 4 lk + v
   const DenseBits B(G);
   const uint32_t rd = B.col_lane(li) + B.rows(lk, 3, 2);
   const uint32_t wr = B.col_lane(li) + B.rows(lk, 2, 2) + (rt0 ? B.row[5] : 0u);
   const uint32_t ncb = (1u << G.c) >> 4;
   const uint32_t trips = (ncb + cbs - 1u) / cbs;  // uniform: barriers inside
-  float sgn = 1.0f;
   for (uint32_t t = blockIdx.x; t < G.n_tiles; t += gridDim.x) {
     const uint32_t base = dense_tile_base(t, G);
-    // Half of the column blocks, picked by a hash, are multiplied by -U and negated:
-    // the bf16 matrix cores round sums down, and with one sign every amplitude of a
-    // state would carry an error of the same direction (a transform circuit of
-    // dense windows on 20 qubits: 5.6e-5 of a mean amplitude in one output instead
-    // of 2e-6).
-    uint32_t hash = (4u * t + cb0) * 0x85ebca6bu;
-    hash = (hash ^ (hash >> 13)) * 0xc2b2ae35u;
-    if ((hash >> 31 ? -1.0f : 1.0f) != sgn) {
-      sgn = -sgn;
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int sl = 0; sl < kSlabs; ++sl) {
-          negate(ur[rt][sl]);
-          negate(ui[rt][sl]);
-        }
-    }
+    if (threadIdx.x == 0) *unfit = 0u;
     if constexpr (kPair) {
       io.put(T, pre);
       if (t + gridDim.x < G.n_tiles) io.issue(G.keep, dense_tile_base(t + gridDim.x, G), pre);
@@ -394,16 +414,20 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
       io.load(G.keep, base, T);
     }
     __syncthreads();
+    bool bad = u_unfit;
     for (uint32_t it = 0; it < trips; ++it) {
       const uint32_t cb = cb0 + it * cbs;
       const bool on = cb < ncb;
       const uint32_t colp = B.col_block(cb);
-      // Ur Xr, Ui Xi, Ur Xi + Ui Xr: the large products and, k = 5, the small ones
-      // by themselves (k = 6: 24 more registers spill, 441 -> 555 us at 27 qubits)
-      f32x4 rr[RT], ii[RT], ri[RT], srr[RT], sii[RT], sri[RT];
+      // real and imaginary: the products of U's large heads with heads, and the others
+      f32x4 hr[RT], hi[RT], sr[RT], si[RT];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) rr[rt] = ii[rt] = ri[rt] = srr[rt] = sii[rt] = sri[rt] = f32x4{0, 0, 0, 0};
+      for (int rt = 0; rt < RT; ++rt) hr[rt] = hi[rt] = sr[rt] = si[rt] = f32x4{0, 0, 0, 0};
+      uint32_t sgn = 0u;
       if (on) {
+        uint32_t never = 0u;
+        asm volatile("" : "+s"(never));
+        float m = 0.0f;
 #pragma unroll
         for (int sl = 0; sl < kSlabs; ++sl) {
           float re[8], im[8];
@@ -412,27 +436,51 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
             const cplx<float> x = T[rd + colp + B.rows(e, 0, 3) + (sl ? B.row[5] : 0u)];
             re[e] = x.re;
             im[e] = x.im;
-            xmax = max3_abs(xmax, x.re, x.im);
+            m = max3_abs(m, x.re, x.im);
           }
-          Split8 xr, xi;
-          split8(re, xr);
-          split8(im, xi);
+          // Half of the columns are multiplied as -X and negated again, by a bit of
+          // the data and one of a hash of the place: with one sign, what is cut
+          // downwards would add up over the amplitudes (a transform circuit of dense
+          // windows on 20 qubits: 5.6e-5 of a mean amplitude in one output instead of
+          // 2e-6) and over the applications of a window.
+          if (sl == 0) {
+            uint32_t hash = (4u * t + cb) * 0x85ebca6bu;
+            hash = (hash ^ (hash >> 13)) * 0xc2b2ae35u;
+            const uint64_t odd = __ballot(__float_as_uint(m) & 1u);
+            const uint32_t col = fold_xor16(odd) ^ (uint32_t)((int32_t)hash >> 31);
+            sgn = (col >> li) << 31;
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            re[e] = __uint_as_float(__float_as_uint(re[e]) ^ sgn);
+            im[e] = __uint_as_float(__float_as_uint(im[e]) ^ sgn);
+          }
+          Split8 x;
+          // h and s += u x, of s the smallest products first
+          auto mul = [&](const SplitU8& u, f32x4& h, f32x4& s) {
+            const u32x4 uh = u.head(never);
+            s = mfma_bf16(u.l, x.h, s);
+            s = mfma_bf16(uh, x.l, s);
+            s = mfma_bf16(u.m, x.m, s);
+            s = mfma_bf16(u.m, x.h, s);
+            s = mfma_bf16(uh, x.m, s);
+            s = mfma_bf16(u.rest, x.h, s);
+            h = mfma_bf16(u.big, x.h, h);
+          };
+          split8(re, x);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
-            f32x4& a = kOwnSmall ? srr[rt] : rr[rt];
-            f32x4& b = kOwnSmall ? sii[rt] : ii[rt];
-            f32x4& c = kOwnSmall ? sri[rt] : ri[rt];
-            a = mfma_small(ur[rt][sl], xr, a);
-            b = mfma_small(ui[rt][sl], xi, b);
-            c = mfma_small(ur[rt][sl], xi, mfma_small(ui[rt][sl], xr, c));
+            mul(ur[rt][sl], hr[rt], sr[rt]);
+            mul(ui[rt][sl], hi[rt], si[rt]);
           }
+          split8(im, x);
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) {
-            rr[rt] = mfma_large(ur[rt][sl], xr, rr[rt]);
-            ii[rt] = mfma_large(ui[rt][sl], xi, ii[rt]);
-            ri[rt] = mfma_large(ur[rt][sl], xi, mfma_large(ui[rt][sl], xr, ri[rt]));
-          }
+          for (int rt = 0; rt < RT; ++rt) mul(ur[rt][sl], hi[rt], si[rt]);
+          negate(x);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) mul(ui[rt][sl], hr[rt], sr[rt]);
         }
+        bad = bad || __any(m >= kSplitMax);
       }
       if constexpr (kPair) __syncthreads();
       if (on) {
@@ -441,12 +489,11 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] =
-                kOwnSmall ? cplx<float>{sgn * ((rr[rt][v] - ii[rt][v]) + (srr[rt][v] - sii[rt][v])),
-                                        sgn * (ri[rt][v] + sri[rt][v])}
-                          : cplx<float>{sgn * (rr[rt][v] - ii[rt][v]), sgn * ri[rt][v]};
+                cplx<float>{__uint_as_float(__float_as_uint(hr[rt][v] + sr[rt][v]) ^ sgn),
+                            __uint_as_float(__float_as_uint(hi[rt][v] + si[rt][v]) ^ sgn)};
       }
     }
-    if (__any(xmax >= kSplitMax) && lane == 0) *unfit = 1u;  // and so for the tiles that follow
+    if (bad && lane == 0) *unfit = 1u;
     __syncthreads();
     if (__builtin_expect(*unfit, 0u)) {
       io.load(false, base, T);  // the state still holds the tile
@@ -613,15 +660,14 @@ bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx
   const uint32_t M = 1u << G.m;
   const size_t lds = sizeof(cplx<R>) * (M + ((M >> 5) << 1)) + sizeof(uint32_t);
   // Two workgroups per CU.  With more, those in flight walk the state further
-  // apart and U is read and split more often (27 qubits complex64, k = 5: 355 us,
-  // with 1024 441, with 2048 398, with one per tile 476; complex128 k = 4 756,
-  // 2048 825); with one, loads are too few (518).  Exceptions, measured the same
-  // way: complex64 k = 4 (8 KB tiles) three (370 us, two 411); complex128 k = 6 one,
-  // what the LDS holds (21 qubits 27 us, two 32); complex64 k = 6 more once a
-  // workgroup would take over 16 tiles (28 qubits: 828 us, two 926; 25 qubits: two 115,
-  // eight 126).
+  // apart and U is read and split more often (27 qubits: complex128 k = 4 756 us,
+  // with 2048 825); with one, loads are too few.  Exceptions, measured the same
+  // way: complex64 k = 4 (8 KB tiles) three (370 us, two 411), and k = 5 up to 2^16
+  // tiles (385 us, two 392; 23 qubits 29 and 30; 28 qubits: 790, two 762); complex128
+  // k = 6 one, what the LDS holds (21 qubits 27 us, two 32); complex64 k = 6 more
+  // once a workgroup would take over 16 tiles (28 qubits: 1022 us, two 1034).
   uint32_t wgs = 512u;
-  if (sizeof(R) == 4 && k == 4) wgs = 768u;
+  if (sizeof(R) == 4 && (k == 4 || (k == 5 && G.n_tiles <= 1u << 16))) wgs = 768u;
   if (sizeof(R) == 4 && k == 6 && G.n_tiles / 16u > wgs) wgs = G.n_tiles / 16u;
   if (sizeof(R) == 8 && k == 6) wgs = 256u;
   const uint32_t grid = G.n_tiles < wgs ? G.n_tiles : wgs;

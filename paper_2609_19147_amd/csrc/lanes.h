@@ -39,4 +39,19 @@ __device__ __forceinline__ uint32_t wave_sum4_value(uint32_t lane) {
   return ((lane >> 3) & 2u) | (lane >> 5);  // rows 0..3: values 0, 2, 1, 3
 }
 
+// The largest of m over the lanes l, l ^ 16, l ^ 32, l ^ 48, and over the wavefront.
+__device__ __forceinline__ float rows_max(float m) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int kN>
+__device__ __forceinline__ float max_row_ror(float m) {
+  return fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x120 + kN, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max(float m) {
+  return max_row_ror<1>(max_row_ror<2>(max_row_ror<4>(max_row_ror<8>(rows_max(m)))));
+}
+
 }  // namespace qs

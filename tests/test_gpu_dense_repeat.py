@@ -1,0 +1,61 @@
+"""Dense complex64 windows applied again and again to the same wires, as Trotter
+steps apply them: the error must not grow faster than that of FP32 products.
+
+The yardstick is those products on the CPU, each multiply-add rounded once to
+float in the order of the FP32 matrix cores' forms.  Both sides start from the
+same float amplitudes and the same float matrix, and the exact result is that
+matrix in complex128.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _window(k, eps, seed):
+    """A unitary within eps of the identity, its entries rounded to float."""
+    rng = np.random.default_rng(seed)
+    h = rng.normal(size=(1 << k, 1 << k)) + 1j * rng.normal(size=(1 << k, 1 << k))
+    w, v = np.linalg.eigh((h + h.conj().T) / 2 / np.sqrt(2 << k))
+    return ((v * np.exp(1j * eps * w)) @ v.conj().T).astype(np.complex64).astype(np.complex128)
+
+
+def _fp32(u, x):
+    """u @ x, four depths at a time: real and imaginary part by two chains of four
+    multiply-adds each (exact products, one rounding to float per addition)."""
+    yr, yi = np.zeros(x.shape, np.float32), np.zeros(x.shape, np.float32)
+
+    def chain(y, a, b):
+        for j in range(a.shape[1]):
+            y = (y.astype(np.float64) + a[:, j:j + 1] * b[j:j + 1]).astype(np.float32)
+        return y
+
+    for j in range(0, u.shape[1], 4):
+        a, b = u[:, j:j + 4], x[j:j + 4]
+        yr = chain(chain(yr, a.real, b.real), a.imag, -b.imag)
+        yi = chain(chain(yi, a.real, b.imag), a.imag, b.real)
+    return yr + 1j * yi.astype(np.float64)
+
+
+@pytest.mark.parametrize("eps", [1e-3, 0.02])
+@pytest.mark.parametrize("k", [5, 6])
+def test_repeated_window_error_is_no_larger_than_fp32(k, eps):
+    import paper_2609_19147_amd as qs
+    n = k + 4
+    u = _window(k, eps, k)
+    psi = W.gaussian_state(n, 3).astype(np.complex64)
+    st = qs.State(n, "c64", init=None)
+    st.upload(psi)
+    plan = qs.Plan(n, [W.G("UNITARY", *range(k), mat=u)])  # the rows are the leading qubits
+    assert [L["kind"] for L in plan.describe()["layers"]] == ["dense"]
+    x = psi.astype(np.complex128).reshape(1 << k, -1)
+    exact, model = x, x
+    for rep in range(1, 401):
+        qs.apply(st, plan)
+        exact, model = u @ exact, _fp32(u, model)
+        if rep in (1, 40, 400):
+            err = np.linalg.norm(st.download().astype(np.complex128) - exact.ravel())
+            ref = np.linalg.norm(model - exact)
+            assert err <= ref, (rep, err, ref)
