@@ -336,13 +336,22 @@ __device__ __forceinline__ void negate(Split8& S) {
   S.l = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, S.l) ^ 0x80008000u);
 }
 // A lane mask folded over the four lanes l, l + 16, ... of a column: 16 bits.
+__device__ __forceinline__ uint32_t fold_or16(uint64_t m) {
+  const uint32_t w = (uint32_t)m | (uint32_t)(m >> 32);
+  return (w | w >> 16) & 0xffffu;
+}
 __device__ __forceinline__ uint32_t fold_xor16(uint64_t m) {
   const uint32_t w = (uint32_t)m ^ (uint32_t)(m >> 32);
   return w ^ w >> 16;
 }
-// The finite floats from here on round to infinity in bf16, and an infinity's
-// remainder is no number: such a tile takes the FP32 forms.
-constexpr float kSplitMax = 0x1.ffp127f;
+// Numbers that the split does not hold: the finite floats from kSplitMax on round
+// to infinity in bf16, and an infinity's remainder is no number; below 2^-109 or
+// so l's last bits are under bf16's range, where the matrix cores take zero (a
+// state of amplitudes around 2^-115 had an error of 1.6e-6, around 2^-120 5e-5).  A
+// tile with a column, or a matrix, whose largest number is not in between (zero
+// apart) takes the FP32 forms; what a column loses is then below 2^-30 of its
+// largest number.
+constexpr float kSplitMax = 0x1.ffp127f, kSplitMin = 0x1p-96f;
 constexpr float kLargeU = 0x1p-3f;  // of U's largest entry
 // max(m, |a|, |b|) in one instruction (fmaxf first canonicalises each operand)
 __device__ __forceinline__ float max3_abs(float m, float a, float b) {
@@ -388,7 +397,7 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
         }
       }
     m = wave_max(m);
-    u_unfit = m >= kSplitMax;
+    u_unfit = m >= kSplitMax || m < kSplitMin;
     const float large = m * kLargeU;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -480,7 +489,8 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) mul(ui[rt][sl], hr[rt], sr[rt]);
         }
-        bad = bad || __any(m >= kSplitMax);
+        bad = bad || __any(m >= kSplitMax) ||
+              (fold_or16(__ballot(m > 0.0f)) & ~fold_or16(__ballot(m >= kSplitMin))) != 0u;
       }
       if constexpr (kPair) __syncthreads();
       if (on) {

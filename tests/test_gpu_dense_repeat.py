@@ -59,3 +59,45 @@ def test_repeated_window_error_is_no_larger_than_fp32(k, eps):
             err = np.linalg.norm(st.download().astype(np.complex128) - exact.ravel())
             ref = np.linalg.norm(model - exact)
             assert err <= ref, (rep, err, ref)
+
+
+@pytest.mark.parametrize("power", [-100, -105, -110, -115])
+@pytest.mark.parametrize("k", [5, 6])
+def test_tiny_states_keep_their_bits(k, power):
+    """A power of two in front of the state changes no significant bit: the error
+    stays within the FP32 chain's, one rounding (half a unit at most, uniform) per
+    product of a complex entry, all at the size of the result."""
+    import paper_2609_19147_amd as qs
+    n = k + 5
+    u = W.random_unitary(1 << k, np.random.default_rng(k)).astype(np.complex64).astype(np.complex128)
+    psi = W.gaussian_state(n, 3).astype(np.complex64) * np.float32(2.0 ** power)
+    st = qs.State(n, "c64", init=None)
+    st.upload(psi)
+    qs.apply(st, qs.Plan(n, [W.G("UNITARY", *range(k), mat=u)]))
+    exact = (u @ psi.astype(np.complex128).reshape(1 << k, -1)).ravel()
+    err = np.linalg.norm(st.download().astype(np.complex128) - exact) / np.linalg.norm(exact)
+    assert err <= np.sqrt(4 * (1 << k) / 2 / 3) * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("k", [5, 6])
+def test_tiny_columns_next_to_ordinary_ones(k):
+    """Some columns of a tile far below the split's range, one empty: every column
+    keeps the accuracy that it has by itself."""
+    import paper_2609_19147_amd as qs
+    n = k + 6
+    u = W.random_unitary(1 << k, np.random.default_rng(k)).astype(np.complex64).astype(np.complex128)
+    psi = W.gaussian_state(n, 5).astype(np.complex64).reshape(1 << k, -1)
+    psi[:, 3] *= np.float32(2.0 ** -110)
+    psi[:, 17] *= np.float32(2.0 ** -113)
+    psi[:, 40] = 0
+    st = qs.State(n, "c64", init=None)
+    st.upload(psi.ravel())
+    qs.apply(st, qs.Plan(n, [W.G("UNITARY", *range(k), mat=u)]))
+    exact = u @ psi.astype(np.complex128)
+    got = st.download().astype(np.complex128).reshape(exact.shape)
+    assert not got[:, 40].any()
+    size = np.linalg.norm(exact, axis=0)
+    size[40] = 1.0
+    err = np.linalg.norm(got - exact, axis=0) / size
+    # twice the rms bound: a column's 2^(k+1) numbers against the mean
+    assert err.max() <= 2 * np.sqrt(4 * (1 << k) / 2 / 3) * 2.0 ** -24, err.max()
