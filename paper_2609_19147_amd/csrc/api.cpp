@@ -616,7 +616,6 @@ namespace {
 // Device scratch for the length of one call that waits for its stream: the
 // state's own area, or, past kKeptScratch bytes, an allocation of the call.
 struct Scratch {
-  static constexpr size_t kKeptScratch = (size_t)64 << 20;
   void* p = nullptr;
   bool own = false;
   Scratch(qs_state& s, size_t bytes) {

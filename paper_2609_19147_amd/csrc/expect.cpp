@@ -133,59 +133,6 @@ ExpectArgs<R> set_args(int n, const TileSet& S, std::vector<const Term*>& order)
   return A;
 }
 
-template <class R>
-void expect_tiled(qs_state& s, const std::vector<Term>& terms, std::vector<double>& out) {
-  const int n = s.n;
-  const uint32_t m = std::min<uint32_t>((uint32_t)n, expect_tile_bits(sizeof(R) == 8));
-  const uint32_t n_tiles = 1u << (n - m);
-  const size_t zmax = n_tiles < kBlocks ? (size_t)8 : kZPieceTerms;
-  std::vector<Piece> pieces;
-  for (const Term& t : terms) {  // sorted by (x, imaginary)
-    const bool imag = (t.ny & 1) != 0;
-    if (pieces.empty() || pieces.back().x != t.x || pieces.back().imag != imag ||
-        pieces.back().terms.size() >= (t.x ? kZPieceTerms : zmax))
-      pieces.push_back({t.x, imag, {}});
-    pieces.back().terms.push_back(&t);
-  }
-  const std::vector<TileSet> sets = make_sets(n, m, pieces);
-  for (size_t s0 = 0; s0 < sets.size(); s0 += kExpectMaxSets) {
-    const size_t ns = std::min<size_t>(kExpectMaxSets, sets.size() - s0);
-    ExpectFold F{};
-    F.n_sets = (uint32_t)ns;
-    std::vector<ExpectArgs<R>> args;
-    std::vector<const Term*> order;
-    uint64_t doubles = 0;
-    for (size_t k = 0; k < ns; ++k) {
-      args.push_back(set_args<R>(n, sets[s0 + k], order));
-      ExpectArgs<R>& A = args.back();
-      const uint32_t nb = std::min(A.n_tiles, kBlocks);
-      A.wsplit = std::min(A.n_win, kBlocks / nb);
-      F.n_terms[k] = A.n_terms;
-      F.n_blocks[k] = nb * A.wsplit;
-      F.off[k] = doubles;
-      doubles += 2ull * F.n_blocks[k] * A.n_terms;
-    }
-    double* buf = (double*)s.ensure_scratch((order.size() + doubles) * sizeof(double));
-    F.partials = buf + order.size();
-    for (size_t k = 0; k < ns; ++k) {
-      args[k].psi = (const cplx<R>*)s.cur_ptr();
-      args[k].partials = buf + order.size() + F.off[k];
-      launch_expect_tiles<R>(args[k], F.n_blocks[k], s.stream);
-    }
-    launch_expect_fold(F, buf, s.stream);
-    std::vector<double> r(order.size());
-    check_hip(hipMemcpyAsync(r.data(), buf, r.size() * sizeof(double), hipMemcpyDeviceToHost, s.stream),
-              "hipMemcpyAsync");
-    s.sync();
-    for (size_t k = 0; k < order.size(); ++k) {
-      if (!order[k]) continue;
-      // both indices of a pair contribute alike; i^ny's sign for two or three Y factors
-      const double f = order[k]->x == 0 ? 1.0 : (order[k]->ny >= 2 ? -2.0 : 2.0);
-      out[order[k]->index] = f * r[k];
-    }
-  }
-}
-
 // One reduction per X mask, eight terms at a time.
 void expect_by_mask(qs_state& s, const std::vector<Term>& terms, std::vector<double>& out) {
   s.ensure_red();
@@ -218,6 +165,79 @@ void expect_by_mask(qs_state& s, const std::vector<Term>& terms, std::vector<dou
     s.sync();
     for (int k = 0; k < nt; ++k) out[terms[t0 + k].index] = o[k];
     t0 = t1;
+  }
+}
+
+template <class R>
+void expect_tiled(qs_state& s, const std::vector<Term>& terms, std::vector<double>& out) {
+  const int n = s.n;
+  const uint32_t m = std::min<uint32_t>((uint32_t)n, expect_tile_bits(sizeof(R) == 8));
+  const uint32_t n_tiles = 1u << (n - m);
+  const size_t zmax = n_tiles < kBlocks ? (size_t)8 : kZPieceTerms;
+  std::vector<Piece> pieces;
+  for (const Term& t : terms) {  // sorted by (x, imaginary)
+    const bool imag = (t.ny & 1) != 0;
+    if (pieces.empty() || pieces.back().x != t.x || pieces.back().imag != imag ||
+        pieces.back().terms.size() >= (t.x ? kZPieceTerms : zmax))
+      pieces.push_back({t.x, imag, {}});
+    pieces.back().terms.push_back(&t);
+  }
+  const std::vector<TileSet> sets = make_sets(n, m, pieces);
+  for (size_t s0 = 0, ns = 0; s0 < sets.size(); s0 += ns) {
+    ExpectFold F{};
+    std::vector<ExpectArgs<R>> args;
+    std::vector<const Term*> order;
+    uint64_t doubles = 0;
+    // as many sets as one launch folds and the kept scratch holds (a set's partials
+    // are 4 MiB at most)
+    for (ns = 0; ns < kExpectMaxSets && s0 + ns < sets.size(); ++ns) {
+      const size_t terms_before = order.size();
+      ExpectArgs<R> A = set_args<R>(n, sets[s0 + ns], order);
+      const uint32_t nb = std::min(A.n_tiles, kBlocks);
+      A.wsplit = std::min(A.n_win, kBlocks / nb);
+      const uint64_t add = 2ull * nb * A.wsplit * A.n_terms;
+      if (ns && (order.size() + doubles + add) * sizeof(double) > kKeptScratch) {
+        order.resize(terms_before);
+        break;
+      }
+      F.n_terms[ns] = A.n_terms;
+      F.n_blocks[ns] = nb * A.wsplit;
+      F.off[ns] = doubles;
+      doubles += add;
+      args.push_back(A);
+    }
+    F.n_sets = (uint32_t)ns;
+    double* buf = nullptr;
+    try {
+      buf = (double*)s.ensure_scratch((order.size() + doubles) * sizeof(double));
+    } catch (const Error&) {
+      // a device without room for it: the reductions need next to none
+      (void)hipGetLastError();
+      std::vector<Term> left;
+      for (size_t k = s0; k < sets.size(); ++k)
+        for (const Piece* p : sets[k].pieces)
+          for (const Term* t : p->terms) left.push_back(*t);
+      std::stable_sort(left.begin(), left.end(), [](const Term& a, const Term& b) { return a.x < b.x; });
+      expect_by_mask(s, left, out);
+      return;
+    }
+    F.partials = buf + order.size();
+    for (size_t k = 0; k < ns; ++k) {
+      args[k].psi = (const cplx<R>*)s.cur_ptr();
+      args[k].partials = buf + order.size() + F.off[k];
+      launch_expect_tiles<R>(args[k], F.n_blocks[k], s.stream);
+    }
+    launch_expect_fold(F, buf, s.stream);
+    std::vector<double> r(order.size());
+    check_hip(hipMemcpyAsync(r.data(), buf, r.size() * sizeof(double), hipMemcpyDeviceToHost, s.stream),
+              "hipMemcpyAsync");
+    s.sync();
+    for (size_t k = 0; k < order.size(); ++k) {
+      if (!order[k]) continue;
+      // both indices of a pair contribute alike; i^ny's sign for two or three Y factors
+      const double f = order[k]->x == 0 ? 1.0 : (order[k]->ny >= 2 ? -2.0 : 2.0);
+      out[order[k]->index] = f * r[k];
+    }
   }
 }
 

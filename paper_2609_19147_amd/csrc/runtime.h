@@ -13,6 +13,12 @@
 #include "planner.h"
 #include "qs.h"
 
+namespace qs {
+// Read-out scratch that a state keeps between calls; a call that needs more
+// allocates and frees it, or works in several steps.
+constexpr size_t kKeptScratch = (size_t)64 << 20;
+}  // namespace qs
+
 // A plan's whole layer sequence recorded as a HIP graph for one state
 // (qs_apply_graph): valid for the plan's parameter version and the buffer the
 // state starts from (gathers flip between the two buffers).
