@@ -176,7 +176,9 @@ void launch_fold_partials(const double* partials, uint64_t count, double* scratc
 // folds them into out[NV] (device), one workgroup per output.
 constexpr int kRedBlocks = 1024;
 constexpr int kMaxTermsPerLaunch = 8;
-template <class R> void launch_norm2(const cplx<R>* psi, uint64_t N, double* partials, double* out, hipStream_t s);
+// others: bytes that the caller's other passes read in turn with psi.
+template <class R>
+void launch_norm2(const cplx<R>* psi, uint64_t N, double* partials, double* out, hipStream_t s, uint64_t others = 0);
 template <class Ra, class Rb>
 void launch_overlap(const cplx<Ra>* a, const cplx<Rb>* b, uint64_t N, double* partials, double* out, hipStream_t s);
 template <class Ra, class Rb>

@@ -948,12 +948,12 @@ double apply_norm2(qs_state& s, qs_plan& p) {
   return o;
 }
 
-double state_norm2(qs_state& s) {
+double state_norm2(qs_state& s, uint64_t others) {
   s.ensure_red();
   if (s.dtype == QS_C64)
-    launch_norm2<float>((const cplx<float>*)s.cur_ptr(), 1ull << s.n, s.red_partials, s.red_out, s.stream);
+    launch_norm2<float>((const cplx<float>*)s.cur_ptr(), 1ull << s.n, s.red_partials, s.red_out, s.stream, others);
   else
-    launch_norm2<double>((const cplx<double>*)s.cur_ptr(), 1ull << s.n, s.red_partials, s.red_out, s.stream);
+    launch_norm2<double>((const cplx<double>*)s.cur_ptr(), 1ull << s.n, s.red_partials, s.red_out, s.stream, others);
   double o;
   check_hip(hipMemcpyAsync(&o, s.red_out, sizeof o, hipMemcpyDeviceToHost, s.stream), "hipMemcpyAsync");
   s.sync();
@@ -969,7 +969,7 @@ std::complex<double> state_overlap(qs_state& a, qs_state& b) {
 }
 
 double state_infidelity(qs_state& a, qs_state& b) {
-  const double na = state_norm2(a), nb = state_norm2(b);
+  const double na = state_norm2(a, b.state_bytes()), nb = state_norm2(b, a.state_bytes());
   if (!(na > 0) || !(nb > 0)) fail(QS_EINVAL, "zero state");
   const std::complex<double> ov = state_overlap(a, b);
   const double ph = std::arg(ov);

@@ -208,7 +208,7 @@ double apply_norm2(qs_state& s, qs_plan& p);
 void apply_graph(qs_state& s, qs_plan& p);
 void free_graphs(qs_state& s);
 void apply_plain_gate(qs_state& s, const NGate& g, const std::vector<double>& params, bool inverse = false);
-double state_norm2(qs_state& s);
+double state_norm2(qs_state& s, uint64_t others = 0);  // others: as of launch_norm2
 std::complex<double> state_overlap(qs_state& a, qs_state& b);
 double state_infidelity(qs_state& a, qs_state& b);
 std::vector<double> state_expect(qs_state& s, const qs_pauli* terms, size_t n_terms);
