@@ -1,6 +1,6 @@
 // Expectations of Pauli sums: terms sorted into tile sets that share a read of
-// the state (k_expect.hip); X masks of more than four bits, and states of fewer
-// than four qubits, take one reduction per mask.
+// the state (k_expect.hip); X masks of more than four bits, states of fewer than
+// four qubits, and a few terms of one mask take one reduction per mask.
 #include <algorithm>
 #include <cmath>
 #include <map>
@@ -262,6 +262,20 @@ std::vector<double> state_expect(qs_state& s, const qs_pauli* terms, size_t n_te
   std::stable_sort(tiled.begin(), tiled.end(), [](const Term& a, const Term& b) {
     return a.x != b.x ? a.x < b.x : (a.ny & 1) < (b.ny & 1);
   });
+  // A few terms of one X mask are one reduction, whose single read of a large state
+  // is faster than the tiles' (one term in us, reduction and tiles: complex64 23
+  // qubits 41 and 44, 25 68 and 74; complex128 24 67 and 71, 26 199 and 267), until
+  // its sums term by term cost more (complex64, 24 qubits: two Z-type terms 51 and
+  // 54, three 55 and 55, two of an X mask 54 and 55; complex128, 26 qubits: eight
+  // Z-type 238 and 276, four of an X mask 210 and 271, eight 297 and 275).  Below 64
+  // MiB both wait for their launches.
+  if (!tiled.empty() && s.state_bytes() >= (64u << 20) && tiled.front().x == tiled.back().x) {
+    const size_t few = s.dtype == QS_C64 ? (tiled.front().x ? 1 : 2) : (tiled.front().x ? 4 : 8);
+    if (tiled.size() <= few) {
+      rest.insert(rest.end(), tiled.begin(), tiled.end());
+      tiled.clear();
+    }
+  }
   std::stable_sort(rest.begin(), rest.end(), [](const Term& a, const Term& b) { return a.x < b.x; });
   if (!tiled.empty()) {
     if (s.dtype == QS_C64) expect_tiled<float>(s, tiled, out);
