@@ -42,6 +42,7 @@ def _fp32(u, x):
 @pytest.mark.parametrize("eps", [1e-3, 0.02])
 @pytest.mark.parametrize("k", [5, 6])
 def test_repeated_window_error_is_no_larger_than_fp32(k, eps):
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     n = k + 4
     u = _window(k, eps, k)
@@ -67,6 +68,7 @@ def test_tiny_states_keep_their_bits(k, power):
     """A power of two in front of the state changes no significant bit: the error
     stays within the FP32 chain's, one rounding (half a unit at most, uniform) per
     product of a complex entry, all at the size of the result."""
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     n = k + 5
     u = W.random_unitary(1 << k, np.random.default_rng(k)).astype(np.complex64).astype(np.complex128)
@@ -83,6 +85,7 @@ def test_tiny_states_keep_their_bits(k, power):
 def test_tiny_columns_next_to_ordinary_ones(k):
     """Some columns of a tile far below the split's range, one empty: every column
     keeps the accuracy that it has by itself."""
+    import torch  # noqa: F401  (its HIP runtime first)
     import paper_2609_19147_amd as qs
     n = k + 6
     u = W.random_unitary(1 << k, np.random.default_rng(k)).astype(np.complex64).astype(np.complex128)
