@@ -794,8 +794,14 @@ Sched make_groups(int n, int tile_bits, int low_bits) {
 // From 23 qubits up 11 bits gain nothing over 12 (shorter runs in the high
 // tiles).  Segments with QFT stages stay at 13 bits (23 qubits: 90 against
 // 108 us, 24: 174 against 179); inverse stages do not (25-qubit phase
-// estimation 699 against 745 us, in complex128 1623 against 1883).
-int fine_tile_bits(int n, int tile_bits) {
+// estimation 699 against 745 us, in complex128 1623 against 1883).  Segments
+// without diagonal layers stay at 13 where that leaves two high groups of five bits
+// (23 qubits), one round and one bit more each: a Walsh layer 89 against 100 us, in
+// complex128 183 against 210, a permuted product layer 256 against 263, but a TFIM
+// step 160 against 144; with a group of six (24 qubits) 183 against 137.
+int fine_tile_bits(int n, int tile_bits, bool diag) {
+  const int rest = n - tile_bits;
+  if (!diag && rest > tile_bits - 4 && rest <= 10) return tile_bits;
   auto groups = [&](int t) { return n <= t ? 1 : 1 + (n - t + t - 5) / (t - 4); };
   int t = tile_bits;
   const int least = n >= 23 ? 12 : 10;
@@ -844,7 +850,8 @@ class Builder {
       : P(P),
         n(P.n),
         wide(make_groups(P.n, tile_bits, low_bits)),
-        fine(make_groups(P.n, P.opt.auto_tile ? fine_tile_bits(P.n, tile_bits) : tile_bits, low_bits)),
+        fine(make_groups(P.n, P.opt.auto_tile ? fine_tile_bits(P.n, tile_bits, true) : tile_bits, low_bits)),
+        plain(make_groups(P.n, P.opt.auto_tile ? fine_tile_bits(P.n, tile_bits, false) : tile_bits, low_bits)),
         window(P.n) {}
 
   void run() {
@@ -917,7 +924,9 @@ class Builder {
   enum Open { NONE, DIAG, WINDOW, PERM, XX, YY };
   PlanIR& P;
   int n;
-  Sched wide, fine;  // tile groups of segments with and without (forward) QFT stages
+  // tile groups of segments with (forward) QFT stages, and without: with and
+  // without diagonal layers
+  Sched wide, fine, plain;
   Open open = NONE;
   std::vector<int> diag, perm, pp;
   std::vector<std::vector<int>> window;
@@ -1186,10 +1195,12 @@ class Builder {
     cancel_butterfly_pairs();
     if (seg.empty()) return;
     size_t N = seg.size();
-    bool qft = false;
-    for (const Item& it : seg)
+    bool qft = false, diag = false;
+    for (const Item& it : seg) {
       qft = qft || (it.ir.type == 0 && P.ops[it.ir.index].kind == OP_QFT);
-    const Sched& sched = qft ? wide : fine;
+      diag = diag || it.ir.type == 1;
+    }
+    const Sched& sched = qft ? wide : (diag ? fine : plain);
     std::vector<std::vector<int>> deps(N);
     for (size_t j = 0; j < N; ++j)
       for (size_t i = 0; i < j; ++i) {
