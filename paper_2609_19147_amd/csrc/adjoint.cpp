@@ -38,6 +38,7 @@ qs_state& work_state(qs_state& psi, int k) {
     s->stream = psi.stream;
     s->buf[0] = alloc_amplitudes(s->state_bytes(), "adjoint work state");
     s->owned[0] = true;
+    s->others = s->state_bytes();  // phi and lambda are undone in turns
     w = std::move(s);
   }
   w->stream = psi.stream;

@@ -252,6 +252,9 @@ extern "C" qs_status qs_batch_create(size_t n_inst, const int* n_qubits, const q
       v->stream = B->stream;
       B->views.push_back(std::move(v));
     }
+    // a group's instances take turns layer by layer
+    for (auto& G : B->groups)
+      for (size_t i : G.inst) B->views[i]->others = (G.inst.size() - 1) * B->views[i]->state_bytes();
     raw = B.release();
     qs_status st = qs_batch_refresh(raw);
     if (st != QS_OK) {

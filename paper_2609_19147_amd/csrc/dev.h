@@ -73,19 +73,6 @@ __device__ __forceinline__ void st_state(T* p, const T& v) {
   else st_nt(p, v);
 }
 
-// Memory that fits the 256 MiB last-level cache, but not the 32 MiB of the eight
-// L2 caches, is best kept there from one pass to the next by cached accesses: an
-// in-place read-and-write of 256 MiB then moves 8.5 TB/s against 6.3 with
-// non-temporal accesses, of 128 MiB 8.2 against 6.4; past the cache it is the
-// other way round (512 MiB: 5.4 against 6.2, 4 GiB: 5.3 against 5.7 TB/s).
-// bytes: what the passes of one stream of work touch again and again.  from: the
-// smallest size at which a kernel gains.  (Gathers, whose two buffers take turns,
-// stream: resident reads gained nothing in complex64, lost 6% in complex128.)
-constexpr uint64_t kResidentBytes = 256ull << 20;
-inline uint32_t keep_resident(uint64_t bytes, uint64_t from = 32ull << 20) {
-  return bytes >= from && bytes <= kResidentBytes ? 1u : 0u;
-}
-
 // Read-only per-launch tables (round and op descriptors, coefficients, count
 // terms) are read through constant-address-space pointers: the compiler then
 // treats them as invariant and uses scalar loads for uniform addresses, which

@@ -661,12 +661,13 @@ DenseGeom dense_geometry(int n, int k, const int* bits_sorted) {
 }
 
 template <class R>
-bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx<R>* U_dev, hipStream_t s) {
+bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx<R>* U_dev, hipStream_t s,
+                  uint64_t others) {
   if (!dense_supported(n, k, sizeof(R) == 8)) return false;
   DenseGeom G = dense_geometry(n, k, bits_sorted);
   // cached reads, streamed writes (a ladder's 24-qubit window passes 65 against
   // 71 us; cached writes 81, the tiles' short runs evicting each other)
-  G.keep = keep_resident(sizeof(cplx<R>) << n);
+  G.keep = keep_resident((uint64_t)sizeof(cplx<R>) << n, others);
   const uint32_t M = 1u << G.m;
   const size_t lds = sizeof(cplx<R>) * (M + ((M >> 5) << 1)) + sizeof(uint32_t);
   // Two workgroups per CU.  With more, those in flight walk the state further
@@ -703,7 +704,7 @@ bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx
   return true;
 }
 
-template bool launch_dense<float>(cplx<float>*, int, int, const int*, const cplx<float>*, hipStream_t);
-template bool launch_dense<double>(cplx<double>*, int, int, const int*, const cplx<double>*, hipStream_t);
+template bool launch_dense<float>(cplx<float>*, int, int, const int*, const cplx<float>*, hipStream_t, uint64_t);
+template bool launch_dense<double>(cplx<double>*, int, int, const int*, const cplx<double>*, hipStream_t, uint64_t);
 
 }  // namespace qs

@@ -265,7 +265,7 @@ template <class R>
 void launch_expect_tiles(const ExpectArgs<R>& A, uint32_t blocks, hipStream_t s) {
   // three terms on 25 complex64 qubits 75 us, streaming 83; XXZ on 24 complex128
   // qubits 394 and 432
-  if (keep_resident((uint64_t)sizeof(cplx<R>) << (A.m + A.n_free), 0))
+  if (keep_resident((uint64_t)sizeof(cplx<R>) << (A.m + A.n_free), 0, 0))
     launch_expect_tiles_k<R, true>(A, blocks, s);
   else
     launch_expect_tiles_k<R, false>(A, blocks, s);

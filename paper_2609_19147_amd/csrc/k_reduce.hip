@@ -371,7 +371,7 @@ void run_reduce(const char* name, F f, uint64_t count, double* partials, double*
 template <class R>
 void launch_norm2(const cplx<R>* psi, uint64_t N, double* partials, double* out, hipStream_t s, uint64_t others) {
   const cplx2<R>* p = reinterpret_cast<const cplx2<R>*>(psi);
-  if (keep_resident(sizeof(cplx<R>) * N + others, 0))
+  if (keep_resident(sizeof(cplx<R>) * N, others, 0))
     run_reduce<1>("reduce_norm2", NormF<R, true>{p}, N / 2, partials, out, s);
   else
     run_reduce<1>("reduce_norm2", NormF<R, false>{p}, N / 2, partials, out, s);
@@ -379,7 +379,7 @@ void launch_norm2(const cplx<R>* psi, uint64_t N, double* partials, double* out,
 
 template <class Ra, class Rb>
 void launch_overlap(const cplx<Ra>* a, const cplx<Rb>* b, uint64_t N, double* partials, double* out, hipStream_t s) {
-  if (keep_resident((sizeof(cplx<Ra>) + sizeof(cplx<Rb>)) * N, 0))
+  if (keep_resident((sizeof(cplx<Ra>) + sizeof(cplx<Rb>)) * N, 0, 0))
     run_reduce<2>("reduce_overlap", OverlapF<Ra, Rb, true>{a, b}, N, partials, out, s);
   else
     run_reduce<2>("reduce_overlap", OverlapF<Ra, Rb, false>{a, b}, N, partials, out, s);
@@ -388,7 +388,7 @@ void launch_overlap(const cplx<Ra>* a, const cplx<Rb>* b, uint64_t N, double* pa
 template <class Ra, class Rb>
 void launch_distance2(const cplx<Ra>* a, const cplx<Rb>* b, uint64_t N, double ar, double ai, double bs,
                       double* partials, double* out, hipStream_t s) {
-  if (keep_resident((sizeof(cplx<Ra>) + sizeof(cplx<Rb>)) * N, 0))
+  if (keep_resident((sizeof(cplx<Ra>) + sizeof(cplx<Rb>)) * N, 0, 0))
     run_reduce<1>("reduce_distance2", DistanceF<Ra, Rb, true>{a, b, ar, ai, bs}, N, partials, out, s);
   else
     run_reduce<1>("reduce_distance2", DistanceF<Ra, Rb, false>{a, b, ar, ai, bs}, N, partials, out, s);

@@ -427,11 +427,11 @@ void launch_diag_k(cplx<R>* psi, uint64_t npairs, const DiagDev& D, hipStream_t 
             dim3(kThreads), 0, s, psi, npairs, D);
 }
 template <class R>
-void launch_diag(cplx<R>* psi, int n, const DiagDev& D, hipStream_t s) {
+void launch_diag(cplx<R>* psi, int n, const DiagDev& D, hipStream_t s, uint64_t others) {
   const uint64_t npairs = (1ull << n) / 2;
   // 24 and 25 complex64 qubits 39 against 48 and 69 against 90 us, 24 complex128 70
   // against 96
-  if (keep_resident(sizeof(cplx<R>) << n))
+  if (keep_resident((uint64_t)sizeof(cplx<R>) << n, others))
     launch_diag_k<R, true>(psi, npairs, D, s);
   else
     launch_diag_k<R, false>(psi, npairs, D, s);
@@ -456,7 +456,7 @@ void launch_gf2(const cplx<R>* in, cplx<R>* out, const Gf2Args& A, hipStream_t s
   template void launch_fill_basis<R>(cplx<R>*, uint64_t, uint64_t, hipStream_t);            \
   template void launch_fill_uniform<R>(cplx<R>*, uint64_t, double, hipStream_t);            \
   template void launch_gather<R>(const cplx<R>*, const uint64_t*, cplx<R>*, uint64_t, hipStream_t); \
-  template void launch_diag<R>(cplx<R>*, int, const DiagDev&, hipStream_t);                 \
+  template void launch_diag<R>(cplx<R>*, int, const DiagDev&, hipStream_t, uint64_t);                \
   template void launch_gf2<R>(const cplx<R>*, cplx<R>*, const Gf2Args&, hipStream_t, double*);
 INST(float)
 INST(double)

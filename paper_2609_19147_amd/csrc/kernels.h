@@ -143,7 +143,7 @@ void launch_batch_observable(const ObsDev* obs_dev, uint32_t count, uint32_t n, 
 size_t batch_observable_partials(uint32_t count, uint32_t n);  // doubles needed for partials
 
 template <class R>
-void launch_diag(cplx<R>* psi, int n, const DiagDev& D, hipStream_t s);
+void launch_diag(cplx<R>* psi, int n, const DiagDev& D, hipStream_t s, uint64_t others);
 
 // Dense k-qubit block (matrix cores): psi <- U on the k bits bits_sorted
 // (ascending); U_dev is 2^k x 2^k row-major in device memory with index bit u
@@ -160,7 +160,8 @@ struct DenseGeom {
 bool dense_supported(int n, int k, bool complex128);
 DenseGeom dense_geometry(int n, int k, const int* bits_sorted);
 template <class R>
-bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx<R>* U_dev, hipStream_t s);
+bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx<R>* U_dev, hipStream_t s,
+                  uint64_t others);
 
 template <class R>
 void launch_gf2(const cplx<R>* in, cplx<R>* out, const Gf2Args& A, hipStream_t s, double* norm_part = nullptr);
@@ -176,7 +177,8 @@ void launch_fold_partials(const double* partials, uint64_t count, double* scratc
 // folds them into out[NV] (device), one workgroup per output.
 constexpr int kRedBlocks = 1024;
 constexpr int kMaxTermsPerLaunch = 8;
-// others: bytes that the caller's other passes read in turn with psi.
+// others (here and below): bytes that the caller's other passes take turns with
+// (keep_resident).
 template <class R>
 void launch_norm2(const cplx<R>* psi, uint64_t N, double* partials, double* out, hipStream_t s, uint64_t others = 0);
 template <class Ra, class Rb>

@@ -633,7 +633,7 @@ namespace {
 // complex64 tile passes keep a state resident from 128 MiB: 25 qubits (256 MiB)
 // 13 TFIM passes 1343 against 1506 us, 24 qubits 740 against 807; at 64 MiB the
 // passes are not bound by memory and streaming is 4% faster.  complex128 passes
-// and the adjoint's two states always stream (24 complex128 qubits: Walsh 8%
+// and the adjoint's fused steps always stream (24 complex128 qubits: Walsh 8%
 // faster resident, Heisenberg 5% slower; two states of 128 MiB 2 to 4% slower).
 constexpr uint64_t kTileResidentFrom = 128ull << 20;
 
@@ -672,7 +672,7 @@ TileKArgs<R> tile_args(qs_state& s, qs_plan& p, int pass) {
   A.n_rounds = d.pass_nrounds[pass];
   A.n = s.n;
   A.scale = d.pass_scale[pass];
-  A.keep = keep_resident(s.state_bytes(), kTileResidentFrom);
+  A.keep = keep_resident(s.state_bytes(), s.others, kTileResidentFrom);
   A.qft = d.pass_qft[pass];
   return A;
 }
@@ -711,7 +711,8 @@ void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* 
     const LayerIR& L = P.layers[li];
     switch (L.kind) {
       case L_DIAG:
-        launch_diag<R>((cplx<R>*)s.cur_ptr(), s.n, diag_dev(d, base, L.index, L.inverse != 0), s.stream);
+        launch_diag<R>((cplx<R>*)s.cur_ptr(), s.n, diag_dev(d, base, L.index, L.inverse != 0), s.stream,
+                       s.others);
         break;
       case L_TILE: {
         TileKArgs<R> A = tile_args<R>(s, p, L.index);
@@ -729,7 +730,7 @@ void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* 
       case L_DENSE: {
         const DenseIR& D = P.denses[L.index];
         const cplx<R>* U = (const cplx<R>*)(base + (L.inverse ? d.dense_mat_dagger[L.index] : d.dense_mat[L.index]));
-        if (!launch_dense<R>((cplx<R>*)s.cur_ptr(), s.n, (int)D.bits.size(), D.bits.data(), U, s.stream)) {
+        if (!launch_dense<R>((cplx<R>*)s.cur_ptr(), s.n, (int)D.bits.size(), D.bits.data(), U, s.stream, s.others)) {
           // the per-gate k-qubit kernel, with the first listed bit most significant
           std::vector<int> desc(D.bits.rbegin(), D.bits.rend());
           launch_matk<R>((cplx<R>*)s.cur_ptr(), s.n, (int)desc.size(), desc.data(), U, s.stream);

@@ -37,6 +37,7 @@ struct qs_state {
   bool owned[2] = {false, false};
   int cur = 0;
   bool view = false;  // owned by a batch
+  uint64_t others = 0;  // bytes of the states that passes over this one take turns with (keep_resident)
   hipStream_t stream = nullptr;
   double* red_partials = nullptr;
   double* red_out = nullptr;
