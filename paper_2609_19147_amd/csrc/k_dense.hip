@@ -277,8 +277,8 @@ dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_, DenseGeom G) {
 //          random unitary            1.5 9.3  34   0.5 3.7   21   0.5  3.1  20
 //   k = 6  window within 1e-3 of 1   2.1  26 119   1.2  31  265   0.3  7.0  68
 //          random unitary            2.0  13  43   1.2 7.4   26   0.6  3.6  16
-// (what is left near the identity is U's rounding to float).  27 qubits: k = 5 385
-// us with six products, 388 now, k = 6 482 and 524.
+// (what is left near the identity is U's rounding to float).  27 qubits: k = 5 376
+// us with six products, 392 now, k = 6 479 and 512.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -344,14 +344,16 @@ __device__ __forceinline__ uint32_t fold_xor16(uint64_t m) {
   const uint32_t w = (uint32_t)m ^ (uint32_t)(m >> 32);
   return w ^ w >> 16;
 }
-// Numbers that the split does not hold: the finite floats from kSplitMax on round
-// to infinity in bf16, and an infinity's remainder is no number; below 2^-109 or
-// so l's last bits are under bf16's range, where the matrix cores take zero (a
-// state of amplitudes around 2^-115 had an error of 1.6e-6, around 2^-120 5e-5).  A
-// tile with a column, or a matrix, whose largest number is not in between (zero
-// apart) takes the FP32 forms; what a column loses is then below 2^-30 of its
-// largest number.
-constexpr float kSplitMax = 0x1.ffp127f, kSplitMin = 0x1p-96f;
+// The split's range.  Below 2^-109 or so l's last bits are under bf16's range, where
+// the matrix cores take zero (a state of amplitudes around 2^-115 had an error of
+// 1.6e-6, around 2^-120 5e-5), and the first steps of an evolution from a basis
+// state are full of such columns: columns whose first 32 rows all lie below
+// kTinyColumn are multiplied by 2^64 (exact), their results by 2^-64.  What the
+// others lose is below 2^-60 of their largest number.  The finite floats from
+// kSplitMax on round to infinity in bf16, and an infinity's remainder is no number: a
+// tile with such a number (scaled, if it is), or a matrix with one or of tiny
+// entries only, takes the FP32 forms.
+constexpr float kSplitMax = 0x1.ffp127f, kTinyColumn = 0x1p-60f, kTinyMatrix = 0x1p-96f;
 constexpr float kLargeU = 0x1p-3f;  // of U's largest entry
 // max(m, |a|, |b|) in one instruction (fmaxf first canonicalises each operand)
 __device__ __forceinline__ float max3_abs(float m, float a, float b) {
@@ -397,7 +399,7 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
         }
       }
     m = wave_max(m);
-    u_unfit = m >= kSplitMax || m < kSplitMin;
+    u_unfit = m >= kSplitMax || m < kTinyMatrix;
     const float large = m * kLargeU;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -432,7 +434,7 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
       f32x4 hr[RT], hi[RT], sr[RT], si[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) hr[rt] = hi[rt] = sr[rt] = si[rt] = f32x4{0, 0, 0, 0};
-      uint32_t sgn = 0u;
+      float scale = 1.0f;
       if (on) {
         uint32_t never = 0u;
         asm volatile("" : "+s"(never));
@@ -457,12 +459,19 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
             hash = (hash ^ (hash >> 13)) * 0xc2b2ae35u;
             const uint64_t odd = __ballot(__float_as_uint(m) & 1u);
             const uint32_t col = fold_xor16(odd) ^ (uint32_t)((int32_t)hash >> 31);
-            sgn = (col >> li) << 31;
+            const uint32_t sgn = (col >> li) << 31;
+            const uint32_t tiny = (~fold_or16(__ballot(m >= kTinyColumn)) >> li & 1u) << 29;  // 64 in the exponent
+            scale = __uint_as_float(0x3f800000u + tiny | sgn);
           }
+          {
+// (as multiply-adds with the split's first differences, the unscaled numbers would
+// stay in registers)
+#pragma clang fp contract(off)
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            re[e] = __uint_as_float(__float_as_uint(re[e]) ^ sgn);
-            im[e] = __uint_as_float(__float_as_uint(im[e]) ^ sgn);
+            for (int e = 0; e < 8; ++e) {
+              re[e] *= scale;
+              im[e] *= scale;
+            }
           }
           Split8 x;
           // h and s += u x, of s the smallest products first
@@ -489,18 +498,17 @@ dense_split_kernel(cplx<float>* __restrict__ psi, const cplx<float>* U_, DenseGe
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) mul(ui[rt][sl], hr[rt], sr[rt]);
         }
-        bad = bad || __any(m >= kSplitMax) ||
-              (fold_or16(__ballot(m > 0.0f)) & ~fold_or16(__ballot(m >= kSplitMin))) != 0u;
+        bad = bad || __any(fabsf(m * scale) >= kSplitMax);
       }
       if constexpr (kPair) __syncthreads();
       if (on) {
+        const float unscale = __uint_as_float(0x7f000000u - __float_as_uint(scale));  // 1 / scale
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             T[wr + colp + B.rows(v, 0, 2) + B.rows(rt, 4, 1)] =
-                cplx<float>{__uint_as_float(__float_as_uint(hr[rt][v] + sr[rt][v]) ^ sgn),
-                            __uint_as_float(__float_as_uint(hi[rt][v] + si[rt][v]) ^ sgn)};
+                cplx<float>{unscale * (hr[rt][v] + sr[rt][v]), unscale * (hi[rt][v] + si[rt][v])};
       }
     }
     if (bad && lane == 0) *unfit = 1u;

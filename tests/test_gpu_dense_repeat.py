@@ -104,3 +104,24 @@ def test_tiny_columns_next_to_ordinary_ones(k):
     err = np.linalg.norm(got - exact, axis=0) / size
     # twice the rms bound: a column's 2^(k+1) numbers against the mean
     assert err.max() <= 2 * np.sqrt(4 * (1 << k) / 2 / 3) * 2.0 ** -24, err.max()
+
+
+@pytest.mark.parametrize("head", [0.0, 2.0 ** -80])
+@pytest.mark.parametrize("big", [1.0, 2.0 ** 70, 2.0 ** 100])
+@pytest.mark.parametrize("k", [5, 6])
+def test_columns_that_start_tiny(k, big, head):
+    """Columns whose leading rows are empty or tiny, the others ordinary or large."""
+    import torch  # noqa: F401  (its HIP runtime first)
+    import paper_2609_19147_amd as qs
+    n = k + 6
+    u = W.random_unitary(1 << k, np.random.default_rng(k)).astype(np.complex64).astype(np.complex128)
+    psi = W.gaussian_state(n, 5).astype(np.complex64).reshape(1 << k, -1)
+    psi[: 1 << (k - 1), ::3] *= np.float32(head)
+    psi[1 << (k - 1):, ::3] *= np.float32(big)
+    st = qs.State(n, "c64", init=None)
+    st.upload(psi.ravel())
+    qs.apply(st, qs.Plan(n, [W.G("UNITARY", *range(k), mat=u)]))
+    exact = u @ psi.astype(np.complex128)
+    got = st.download().astype(np.complex128).reshape(exact.shape)
+    err = np.linalg.norm(got - exact, axis=0) / np.linalg.norm(exact, axis=0)
+    assert err.max() <= 2 * np.sqrt(4 * (1 << k) / 2 / 3) * 2.0 ** -24, err.max()
