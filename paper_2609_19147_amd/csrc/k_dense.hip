@@ -30,11 +30,11 @@
 // and tables in the tile loop and 2048 workgroups, and now:
 //             complex64                      complex128
 //   n      k=4       k=5       k=6       k=4       k=5        k=6
-//   16   5.6 4.7   8.0 6.5  15.2  9.5  6.2 5.2  10.0 7.6   20.4 13.7
-//   22    18  14    29  18    40   23    28  22    45  32     83   51
-//   25   106  73   122  79   195  128   210 183   249 195    454  312
-//   27   426 371   438 360   679  445   865 756   942 805   1646 1206
-// (27 qubits complex64: 2.1 GB moved, 5.8, 6.0 and 4.8 TB/s; a copy of this
+//   16   5.4 4.1   8.1 6.7  15.3 11.1  6.4 5.0  10.1 7.1   20.6 14.3
+//   22    20  15    30  18    42   27    30  24    49  32     85   52
+//   25   108  83   123  90   194  133   204 179   250 198    451  308
+//   27   440 375   446 393   681  527   857 743   933 822   1633 1206
+// (27 qubits complex64: 2.1 GB moved, 5.7, 5.5 and 4.1 TB/s; a copy of this
 // size reaches 5.65.)
 //
 // Operand layouts of V_MFMA_{F32,F64}_16X16X4 (wave64): A[i][kk] in lane
@@ -277,8 +277,8 @@ dense_kernel(cplx<R>* __restrict__ psi, const cplx<R>* U_, DenseGeom G) {
 //          random unitary            1.5 9.3  34   0.5 3.7   21   0.5  3.1  20
 //   k = 6  window within 1e-3 of 1   2.1  26 119   1.2  31  265   0.3  7.0  68
 //          random unitary            2.0  13  43   1.2 7.4   26   0.6  3.6  16
-// (what is left near the identity is U's rounding to float).  27 qubits: k = 5 376
-// us with six products, 392 now, k = 6 479 and 512.
+// (what is left near the identity is U's rounding to float).  27 qubits: k = 5 379
+// us with six products, 393 now, k = 6 487 and 527.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -681,10 +681,11 @@ bool launch_dense(cplx<R>* psi, int n, int k, const int* bits_sorted, const cplx
   // Two workgroups per CU.  With more, those in flight walk the state further
   // apart and U is read and split more often (27 qubits: complex128 k = 4 756 us,
   // with 2048 825); with one, loads are too few.  Exceptions, measured the same
-  // way: complex64 k = 4 (8 KB tiles) three (370 us, two 411), and k = 5 up to 2^16
-  // tiles (385 us, two 392; 23 qubits 29 and 30; 28 qubits: 790, two 762); complex128
-  // k = 6 one, what the LDS holds (21 qubits 27 us, two 32); complex64 k = 6 more
-  // once a workgroup would take over 16 tiles (28 qubits: 1022 us, two 1034).
+  // way: complex64 k = 4 (8 KB tiles) three (375 us, two 416), and k = 5 up to 2^16
+  // tiles (22 qubits 17.7 us, two 19.1; 25 qubits 90.0 and 90.9; 27 qubits 393 and
+  // 389; 28 qubits 791 and 761); complex128 k = 6 one, what the LDS holds (21 qubits
+  // 27 us, two 32); complex64 k = 6 more once a workgroup would take over 16 tiles
+  // (28 qubits: 1030 us, two 1034).
   uint32_t wgs = 512u;
   if (sizeof(R) == 4 && (k == 4 || (k == 5 && G.n_tiles <= 1u << 16))) wgs = 768u;
   if (sizeof(R) == 4 && k == 6 && G.n_tiles / 16u > wgs) wgs = G.n_tiles / 16u;

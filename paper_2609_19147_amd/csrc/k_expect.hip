@@ -18,8 +18,9 @@
 // compensated over the workgroup's tiles and over the workgroups; all in FP64.
 //
 // Bound by vector instructions (per 16 amplitudes about 80 per X mask, of which
-// 32 are conversions to FP64, and 20 per term), beside one read of the state
-// per tile set.  26-qubit XXZ chain in complex64 (75 terms, 26 X masks, four
+// 32 are conversions to FP64, and 20 per term; 67% of the SIMDs' cycles at 26
+// qubits) and nearly as many scalar ones, beside one read of the state per tile
+// set.  26-qubit XXZ chain in complex64 (75 terms, 26 X masks, four
 // sets): 29 reductions and host round trips 3.83 ms -> 1.00 ms; 10 qubits, 19
 // terms: 12 reductions, 0.31 ms of wall time -> 0.03 ms.  The products from
 // registers holding a whole window took 200 registers and 2.3 ms; 2^13 tiles

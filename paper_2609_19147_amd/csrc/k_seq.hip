@@ -9,7 +9,9 @@
 // and sums every layer's cross densities on the way.
 //
 // Bound by the latency of the rounds (one workgroup, one to four waves per
-// SIMD).  12-qubit, 8-layer ansatz in complex128: energy and gradient 810 us in
+// SIMD): 10 qubits complex64 33% of the wavefront's cycles issue vector
+// instructions and 44% wait, 12 qubits complex128 22 and 53%, its backward sweep 19
+// and 50%.  12-qubit, 8-layer ansatz in complex128: energy and gradient 810 us in
 // 53 launches -> 620 us in seven; 10-qubit TFIM, 20 Strang steps (five passes):
 // 90 -> 74 us.
 #include "kernels.h"

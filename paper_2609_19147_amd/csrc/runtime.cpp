@@ -167,12 +167,13 @@ void round_pass_unitaries(const TilePassIR& T, const std::vector<TileRound>& rou
 
 // Neighbouring rounds over the same register bits, QFT stages among them, become
 // one RT_CHAIN where the kernel has no straight-line code for them: each round
-// less is a read and a write of the tile in LDS and a barrier less (27-qubit
-// complex128 QFT, Walsh layer and permutation, two of its three passes with five
-// rounds over two sets of bits: 4000 us, as two rounds each 3600; inverse QFT on
-// 28 qubits complex64, whose stages are all rounds of one: 3403 against 2618).  A
-// Hadamard moves up to the last op before it that acts
-// on its bit or reads it: right behind its QFT stage the two run as one.
+// less is a read and a write of the tile in LDS and a barrier less.  With the
+// kernels without QFT code for the other passes, 27-qubit complex128 QFT, Walsh
+// layer and permutation (two of its three passes with five rounds over two sets of
+// bits) went from 3900 to 3500 us, an inverse QFT on 28 qubits complex64, whose
+// stages are all rounds of one, from 3400 to 2635; 30 qubits complex64, bound by
+// HBM, 13160 and 13130.  A Hadamard moves up to the last op before it that acts on
+// its bit or reads it: right behind its QFT stage the two run as one.
 void chain_rounds(std::vector<TileRound>& rounds, std::vector<TileOp>& ops) {
   auto stage = [&](int k) { return ops[k].kind == OP_QFT || ops[k].kind == OP_QFT_INV; };
   auto chainable = [&](const TileRound& r) {
