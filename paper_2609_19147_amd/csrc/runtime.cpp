@@ -695,13 +695,15 @@ void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* 
     // gather than a launch of its own (us, apart and as one: complex64 9 qubits 14.5
     // and 12.6, 10 11.3 and 13.7, 11 13.0 and 14.1, 12 15.8 and 15.2; complex128 9
     // 15.8 and 15.3, 10 16.4 and 18.2, 13 28.1 and 29.8; with a second pass 10 qubits
-    // 25.3 and 24.6, 13 47.6 and 43.3; two passes 10 qubits 48.8 and 40.7)
+    // 25.3 and 24.6, 13 47.6 and 43.3; two passes 10 qubits 48.8 and 40.7).  A state
+    // without a second buffer needs none in a sequence, and gets none for this.
     if (!d.seq_layer.empty()) {
       const size_t end = norm_last ? last - 1 : last;
       size_t e = li;
       bool gather = false;
       for (; e < end && d.seq_layer[e]; ++e) gather = gather || P.layers[e].kind == L_GF2;
-      const bool apart = gather && e - li == 2 && s.n >= 10 && (sizeof(R) == 8 || s.n <= 11);
+      const bool apart =
+          gather && e - li == 2 && s.n >= 10 && (sizeof(R) == 8 || s.n <= 11) && s.buf[1 - s.cur];
       if (e - li >= 2 && !apart) {
         launch_seq<R>((cplx<R>*)s.cur_ptr(), s.n, (const SeqStep<R>*)(base + d.seq) + li, (uint32_t)(e - li),
                       d.blob, d.bytes, s.stream);

@@ -36,3 +36,25 @@ def test_runs_of_layers(kind, n, dtype):
     # a float (double) rounding or two per gate, all of the size of the state
     eps = 2.0 ** -24 if dtype == "c64" else 2.0 ** -53
     assert np.linalg.norm(st.download() - ref) <= 4 * np.sqrt(len(gates)) * 4 * eps
+
+
+@pytest.mark.parametrize("kind", ["pass_gather", "gather_pass"])
+def test_a_state_of_one_buffer_stays_in_it(kind):
+    """Nothing is allocated for a pair that a sequence runs in place (a capture or a memory cap may forbid it)."""
+    import torch  # noqa: F401  (its HIP runtime first)
+    import paper_2609_19147_amd as qs
+    n = 10
+    rng = np.random.default_rng(n)
+    u = [W.G("U", q, mat=W.random_unitary(2, rng)) for q in range(n)]
+    perm = W.random_perm_block(n, 40, 1)
+    gates = u + perm if kind == "pass_gather" else perm + u
+    psi = W.gaussian_state(n, n)
+    st = qs.State(n, "c128", init=None, lazy_scratch=True).upload(psi)
+    plan = qs.Plan(n, gates, window_k=-1)
+    held = qs.memory_info()[0]
+    for _ in range(2):
+        qs.apply(st, plan)
+    torch.cuda.synchronize()
+    assert qs.memory_info()[0] == held
+    ref = sv.run(sv.run(psi, n, gates), n, gates)
+    assert np.linalg.norm(st.download() - ref) <= 4 * np.sqrt(2 * len(gates)) * 4 * 2.0 ** -53
