@@ -683,7 +683,8 @@ template TileKArgs<double> tile_args<double>(qs_state&, qs_plan&, int);
 namespace {
 
 template <class R>
-void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* norm_last = nullptr) {
+void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* norm_last = nullptr,
+                    bool in_place = false) {
   const PlanDev& d = p.device_for(s.dtype);
   const char* base = (const char*)d.blob;
   const PlanIR& P = p.ir;
@@ -696,14 +697,15 @@ void apply_layers_t(qs_state& s, qs_plan& p, size_t first, size_t last, double* 
     // and 12.6, 10 11.3 and 13.7, 11 13.0 and 14.1, 12 15.8 and 15.2; complex128 9
     // 15.8 and 15.3, 10 16.4 and 18.2, 13 28.1 and 29.8; with a second pass 10 qubits
     // 25.3 and 24.6, 13 47.6 and 43.3; two passes 10 qubits 48.8 and 40.7).  A state
-    // without a second buffer needs none in a sequence, and gets none for this.
+    // without a second buffer needs none in a sequence, and gets none for this; one
+    // recorded by a caller's capture stays in its buffer, from replay to replay.
     if (!d.seq_layer.empty()) {
       const size_t end = norm_last ? last - 1 : last;
       size_t e = li;
       bool gather = false;
       for (; e < end && d.seq_layer[e]; ++e) gather = gather || P.layers[e].kind == L_GF2;
       const bool apart =
-          gather && e - li == 2 && s.n >= 10 && (sizeof(R) == 8 || s.n <= 11) && s.buf[1 - s.cur];
+          gather && e - li == 2 && s.n >= 10 && (sizeof(R) == 8 || s.n <= 11) && s.buf[1 - s.cur] && !in_place;
       if (e - li >= 2 && !apart) {
         launch_seq<R>((cplx<R>*)s.cur_ptr(), s.n, (const SeqStep<R>*)(base + d.seq) + li, (uint32_t)(e - li),
                       d.blob, d.bytes, s.stream);
@@ -832,15 +834,17 @@ double distance_t(qs_state& a, qs_state& b, double ar, double ai, double bs) {
 void apply_layers(qs_state& s, qs_plan& p, size_t first, size_t last, bool track) {
   const Range range("qs.apply");
   s.plain_acc = NormAcc{};  // plain layers' rounding compensation restarts with every call
+  bool in_place = false;
   if (track) {
     // nothing is recorded into a stream that is being captured
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     check_hip(hipStreamIsCapturing(s.stream, &cs), "hipStreamIsCapturing");
     track = cs == hipStreamCaptureStatusNone;
+    in_place = !track;
   }
   if (track) p.acquire(s.dtype, s.stream);
-  if (s.dtype == QS_C64) apply_layers_t<float>(s, p, first, last);
-  else apply_layers_t<double>(s, p, first, last);
+  if (s.dtype == QS_C64) apply_layers_t<float>(s, p, first, last, nullptr, in_place);
+  else apply_layers_t<double>(s, p, first, last, nullptr, in_place);
   if (track) p.release(s.dtype, s.stream);
 }
 

@@ -58,3 +58,31 @@ def test_a_state_of_one_buffer_stays_in_it(kind):
     assert qs.memory_info()[0] == held
     ref = sv.run(sv.run(psi, n, gates), n, gates)
     assert np.linalg.norm(st.download() - ref) <= 4 * np.sqrt(2 * len(gates)) * 4 * 2.0 ** -53
+
+
+@pytest.mark.parametrize("kind", ["pass_gather", "gather_pass"])
+def test_a_captured_pair_goes_on_from_replay_to_replay(kind):
+    """Recorded by the caller's own capture, a pair that a sequence runs in place reads its last result."""
+    import torch
+    import paper_2609_19147_amd as qs
+    n = 10
+    rng = np.random.default_rng(n)
+    u = [W.G("U", q, mat=W.random_unitary(2, rng)) for q in range(n)]
+    perm = W.random_perm_block(n, 40, 1)
+    gates = u + perm if kind == "pass_gather" else perm + u
+    psi = W.gaussian_state(n, n)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        st = qs.State(n, "c128", init=None).upload(psi)
+        plan = qs.Plan(n, gates, window_k=-1)
+        qs.apply(st, plan)
+    torch.cuda.synchronize()
+    ref = sv.run(psi, n, gates)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        qs.apply(st, plan)
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = sv.run(ref, n, gates)
+        assert np.linalg.norm(st.download() - ref) <= 4 * np.sqrt((k + 2) * len(gates)) * 4 * 2.0 ** -53, k
