@@ -377,6 +377,7 @@ void build_blob(const qs_plan& p, PlanDev& d, Blob& b) {
       bool sym = true;
       for (int st = r.op_begin; st < r.op_end && sym; ++st) {
         const TileOp& op = T.ops[st];
+        if (op.kind != OP_QFT) continue;  // a Hadamard has no coefficients
         const int h = (1 << op.rbit) / 2;
         for (int k = 0; k < h && sym; ++k)
           sym = std::abs(coef[op.coef + k] * cd(0.0, 1.0) - coef[op.coef + k + h]) <= 1e-14;
